@@ -12,6 +12,7 @@
 #include <mutex>
 #include <string>
 #include <type_traits>
+#include <utility>
 
 #include "../../include/cslbm.h"
 #include "cm_collide.hpp"
@@ -682,17 +683,26 @@ int cslbm_step(cslbm_level* L, int32_t n_steps, hipStream_t stream)
             return fail(CSLBM_ERR_ARG, "gmax_running needs gmax_buf");
     }
 
-    for (int n = 0; n < n_steps; ++n) {
+    auto swap_buffers = [&]() {
+        std::swap(L->f, L->f_next);
+        std::swap(L->g, L->g_next);
+    };
+    int n = 0;
+    // fused pairs: an even number of them, so that the buffers' roles after
+    // n_steps are those of n_steps single steps, and at least one single step
+    // after them, so that f_next holds the state before the last step
+    if (n_steps >= 5 && step_pair_applies(L))
+        for (const int paired = (n_steps - 1) / 4 * 4; n < paired; n += 2) {
+            rc = launch_step_pair(L, L->f, L->f_next, L->g, L->g_next, stream);
+            if (rc) return rc;
+            swap_buffers();
+        }
+    for (; n < n_steps; ++n) {
         rc = grad ? launch_step_grad(L, L->f, L->f_next, L->g, L->g_next, L->vel, L->vel_next, stream)
                   : launch_step_into(L, L->f, L->f_next, L->g, L->g_next, stream);
         if (rc) return rc;
         if (grad) std::swap(L->vel, L->vel_next);
-        void* t = L->f;
-        L->f = L->f_next;
-        L->f_next = t;
-        float* tg = L->g;
-        L->g = L->g_next;
-        L->g_next = tg;
+        swap_buffers();
     }
     return CSLBM_OK;
 }

@@ -52,6 +52,12 @@ dim3 step_block(int nx);
 int launch_step_into(const cslbm_level* L, const void* fin, void* fout, const float* gin,
                      float* gout, hipStream_t stream);
 
+// Two such steps in one launch, the state between them kept on the chip
+// (step_pair.hip), for levels step_pair_applies accepts.
+bool step_pair_applies(const cslbm_level* L);
+int launch_step_pair(const cslbm_level* L, const void* fin, void* fout, const float* gin, float* gout,
+                     hipStream_t stream);
+
 // One step in the finite-difference gradient mode (grad_mode 1): the
 // adaptive factor takes |grad u|_F of vel, the input state's velocity, and
 // the new state's velocity goes to vel_out.  With gmax_running the field

@@ -1,0 +1,392 @@
+// step_pair.hip -- two collide-stream steps of a fully periodic FP32 level in
+// one pass over memory (gfx950).
+//
+// k_step is bound by HBM: 27 reads and 27 writes per lattice update, at the
+// rate its access pattern reaches without any arithmetic.  Here a workgroup
+// walks a column of cells (a TX x TY tile of the x-y plane) along z.  For
+// every plane it computes the first step on the tile and one cell around it
+// (one thread per cell), puts the new populations of that plane into LDS, and
+// its output threads take the second step's pulled populations from there:
+// those with c_z = -1 complete the output plane below, those with c_z = 0 and
+// +1 wait in 27 registers for the planes to come.  A pair of steps reads the
+// state once and writes it once; what it pays is the first step of the
+// halo cells (a tile's perimeter, and two planes per workgroup).  One plane
+// of LDS per workgroup, two barriers per plane.
+//
+// What bounds it: at 256^3 the VALU is busy about 70 % of the time and HBM
+// moves 4.1 TB/s, so neither alone; the loads of the next plane are in
+// flight during the second step only.  Fetching earlier (before the barrier,
+// or before the first step) needs 27 more registers: three waves per SIMD or
+// spills, both slower (487 -> 530-580 us per step at 256^3).  Per step,
+// pair against k_step: 486 / 642 us at 256^3, 53 / 82 us at 128^3, 54 /
+// 105 us at 181x118x77 (rows off the cache lines); with force and scalar 84 /
+// 108 us at 128^3.  binary16 levels stay with k_step, which the VALU already
+// limits.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+
+#include "../../include/cslbm.h"
+#include "cm_collide.hpp"
+#include "exchange.hpp"
+#include "internal.hpp"
+#include "lattice.hpp"
+
+namespace cslbm {
+
+struct PairArgs {
+    const float* f;
+    float* fo;
+    const float* g;
+    float* go;
+    const float* force;
+    int nx, ny, nz;
+    int ntx, nty;   // tiles along x and y
+    int ty;         // rows of a tile (at most TY)
+    int cz;         // output planes of a workgroup
+    int64_t plane;
+    Rates r;
+    float beta, s_ref, inv_tau_s;
+};
+
+template <int TX, int TY>
+struct PairShape {
+    static constexpr int RX = TX + 2, RY = TY + 2;
+    static constexpr int kRegion = RX * RY;   // first-step cells of a plane
+    static constexpr int kThreads = (kRegion + 63) / 64 * 64;   // of a full-height tile
+};
+
+// Uniform plane bases stay in one SGPR pair that walks from plane to plane,
+// and a lane adds its 32-bit byte offset.  The empty asm statements keep the
+// compiler from forming 27 bases ahead of the z loop (they spilled into
+// VGPR lanes) or one 64-bit lane address per plane.
+using GlobalFloat = __attribute__((address_space(1))) float;
+using GlobalChar = __attribute__((address_space(1))) char;
+
+struct PlaneWalk {
+    int64_t at = 0, step;   // bytes
+    __device__ __forceinline__ explicit PlaneWalk(int64_t plane) : step(plane * 4) {}
+    __device__ __forceinline__ void next()
+    {
+        at += step;
+        asm volatile("" : "+s"(at));
+    }
+    __device__ __forceinline__ GlobalFloat* lane(const float* base, uint32_t off) const
+    {
+        GlobalChar* b = (GlobalChar*)base + at;
+        asm volatile("" : "+s"(b));
+        return (GlobalFloat*)(b + off);
+    }
+};
+
+template <bool kForce, bool kScalar, int TX, int TY, int kWaves, int kPerCu>
+__global__ void __launch_bounds__((PairShape<TX, TY>::kThreads))
+    __attribute__((amdgpu_waves_per_eu(kWaves))) k_step_pair(const PairArgs a)
+{
+    using S = PairShape<TX, TY>;
+    constexpr int R = S::kRegion;
+    __shared__ float lds[(kScalar ? Q + QS : Q) * R];
+
+    const int nx = a.nx, ny = a.ny, nz = a.nz;
+    const int64_t nxy = (int64_t)nx * ny;
+    const int64_t P = a.plane;
+    // x-fastest tiles, each XCD a contiguous range: neighbouring tiles walk z
+    // side by side on one XCD and find their shared lines in its L2
+    const int blk = xcd_block(blockIdx.x, gridDim.x);
+    const int bx = blk % a.ntx, by = (blk / a.ntx) % a.nty, bz = blk / (a.ntx * a.nty);
+    const int t = threadIdx.x;
+    // first-step cell of this thread and its pull offsets (threads past the
+    // tile's rows repeat cells of the last row and store nothing)
+    const int rx = t % S::RX, ry = min(t / S::RX, S::RY - 1);
+    const bool in_region = t < (a.ty + 2) * S::RX;
+    const int x = ((bx * TX - 1 + rx) % nx + nx) % nx;
+    const int y = ((by * a.ty - 1 + ry) % ny + ny) % ny;
+    const int xs[3] = {x == nx - 1 ? 0 : x + 1, x, x == 0 ? nx - 1 : x - 1};
+    const int ys[3] = {(y == ny - 1 ? 0 : y + 1) * nx, y * nx, (y == 0 ? ny - 1 : y - 1) * nx};
+    // second-step cell.  With two workgroups on a CU, every second round of
+    // 256 workgroups leaves its first waves idle instead of its last, so
+    // that the two leave different SIMDs idle
+    const int t2 = t - (kPerCu == 2 && ((blockIdx.x >> 8) & 1) ? (int)blockDim.x - ((a.ty * TX + 63) & ~63) : 0);
+    const int ox = t2 & (TX - 1), oy = t2 >= 0 ? t2 / TX : a.ty;
+    const int X = bx * TX + ox, Y = by * a.ty + oy;
+    const bool out = oy < a.ty && X < nx && Y < ny;
+    const uint32_t ocell = (uint32_t)(X + nx * Y) * 4u;
+    float* const wr = lds + t;
+    const float* const rd = lds + (oy + 1) * S::RX + ox + 1;
+    const int z0 = bz * a.cz, z1 = min(z0 + a.cz, nz);
+
+    float pre[27], gpre[QS], fpre[3];   // first-step cell: pulled, then collided
+    auto fetch = [&](int p) {
+        const int z = p < 0 ? p + nz : (p >= nz ? p - nz : p);
+        // formed again for every plane: kept across the loop they are nine
+        // 64-bit lane offsets
+        int qx[3] = {xs[0], xs[1], xs[2]}, qy[3] = {ys[0], ys[1], ys[2]};
+        asm volatile("" : "+v"(qx[0]), "+v"(qx[1]), "+v"(qx[2]), "+v"(qy[0]), "+v"(qy[1]), "+v"(qy[2]));
+        const int64_t zo[3] = {(z == nz - 1 ? 0 : z + 1) * nxy, z * nxy, (z == 0 ? nz - 1 : z - 1) * nxy};
+        const float* const fz[3] = {a.f + zo[0], a.f + zo[1], a.f + zo[2]};
+        PlaneWalk w(P);
+#pragma unroll
+        for (int i = 0; i < Q; ++i) {
+            pre[tensor_slot(i)] = *w.lane(fz[kCz[i] + 1], (uint32_t)(qx[kCx[i] + 1] + qy[kCy[i] + 1]) * 4u);
+            w.next();
+        }
+        if (kScalar) {
+            const float* const gz[3] = {a.g + zo[0], a.g + zo[1], a.g + zo[2]};
+            PlaneWalk wg(P);
+#pragma unroll
+            for (int i = 0; i < QS; ++i) {
+                gpre[i] = *wg.lane(gz[kSz[i] + 1], (uint32_t)(qx[kSx[i] + 1] + qy[kSy[i] + 1]) * 4u);
+                wg.next();
+            }
+        }
+        if (kForce) {
+            PlaneWalk wf(P);
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                fpre[d] = *wf.lane(a.force + zo[1], (uint32_t)(qx[1] + qy[1]) * 4u);
+                wf.next();
+            }
+        }
+    };
+    // Waits for the fetched plane.  Placed before the stores of a plane, so
+    // that the next plane's collision does not wait for those stores as well
+    // (loads and stores share one counter).
+    auto arrived = [&]() {
+#pragma unroll
+        for (int q = 0; q < 27; q += 9)
+            asm volatile("" : : "v"(pre[q]), "v"(pre[q + 1]), "v"(pre[q + 2]), "v"(pre[q + 3]), "v"(pre[q + 4]),
+                         "v"(pre[q + 5]), "v"(pre[q + 6]), "v"(pre[q + 7]), "v"(pre[q + 8]));
+        if (kScalar)
+            asm volatile("" : : "v"(gpre[0]), "v"(gpre[1]), "v"(gpre[2]), "v"(gpre[3]), "v"(gpre[4]),
+                         "v"(gpre[5]), "v"(gpre[6]));
+        if (kForce) asm volatile("" : : "v"(fpre[0]), "v"(fpre[1]), "v"(fpre[2]));
+    };
+    // the cell update of k_step on pulled populations
+    auto collide = [&](float (&v)[27], float (&gv)[QS], const float (&F)[3]) {
+        float s = 0.0f;
+        float Fz = F[2];
+        if (kScalar) {
+            s = (gv[0] + (gv[1] + gv[2])) + ((gv[3] + gv[4]) + (gv[5] + gv[6]));
+            Fz += a.beta * (s - a.s_ref);
+        }
+        const CellMacro mc = cm_collide(v, a.r, F[0], F[1], Fz);
+        if (kScalar)
+#pragma unroll
+            for (int i = 0; i < QS; ++i) {
+                const float ge = scalar_eq(i, s, mc.ux, mc.uy, mc.uz);
+                gv[i] = gv[i] - (gv[i] - ge) * a.inv_tau_s;
+            }
+    };
+
+    // second-step populations gathered so far.  now: output plane p - 1 (those
+    // with c_z = +1 and 0 already read); later: output plane p (c_z = +1)
+    float now[27], later[9], gnow[QS], glater = 0.0f;
+#pragma unroll
+    for (int q = 0; q < 27; ++q) now[q] = 0.0f;
+#pragma unroll
+    for (int q = 0; q < 9; ++q) later[q] = 0.0f;
+#pragma unroll
+    for (int q = 0; q < QS; ++q) gnow[q] = 0.0f;
+
+    fetch(z0 - 1);
+    arrived();
+    for (int p = z0 - 1; p <= z1; ++p) {
+        // first step on plane p
+        float F1[3] = {0.0f, 0.0f, 0.0f};
+        if (kForce)
+#pragma unroll
+            for (int d = 0; d < 3; ++d) F1[d] = fpre[d];
+        collide(pre, gpre, F1);
+        __syncthreads();   // the previous plane has been read
+        if (in_region) {
+#pragma unroll
+            for (int i = 0; i < Q; ++i) wr[i * R] = pre[tensor_slot(i)];
+            if (kScalar)
+#pragma unroll
+                for (int i = 0; i < QS; ++i) wr[(Q + i) * R] = gpre[i];
+        }
+        __syncthreads();
+        // without a branch: a conditional fetch keeps both versions of the
+        // registers (past the last plane it reloads that plane)
+        fetch(min(p + 1, z1));
+        // second step on output plane p - 1
+        const bool store = out && p > z0;
+        if (store) {
+#pragma unroll
+            for (int i = 0; i < Q; ++i)
+                if (kCz[i] == -1) now[tensor_slot(i)] = rd[i * R - kCx[i] - kCy[i] * S::RX];
+            if (kScalar) gnow[6] = rd[(Q + 6) * R];
+            float F2[3] = {0.0f, 0.0f, 0.0f};
+            if (kForce) {
+                PlaneWalk w(P);
+#pragma unroll
+                for (int d = 0; d < 3; ++d) {
+                    F2[d] = *w.lane(a.force + (p - 1) * nxy, ocell);
+                    w.next();
+                }
+            }
+            collide(now, gnow, F2);
+        }
+        arrived();
+        if (store) {
+            uint32_t oc = ocell;
+            asm volatile("" : "+v"(oc));
+            PlaneWalk w(P);
+#pragma unroll
+            for (int i = 0; i < Q; ++i) {
+                __builtin_nontemporal_store(now[tensor_slot(i)], w.lane(a.fo + (p - 1) * nxy, oc));
+                w.next();
+            }
+            if (kScalar) {
+                PlaneWalk wg(P);
+#pragma unroll
+                for (int i = 0; i < QS; ++i) {
+                    __builtin_nontemporal_store(gnow[i], wg.lane(a.go + (p - 1) * nxy, oc));
+                    wg.next();
+                }
+            }
+        }
+        if (out) {
+            int k = 0;
+#pragma unroll
+            for (int i = 0; i < Q; ++i)
+                if (kCz[i] == 0) now[tensor_slot(i)] = rd[i * R - kCx[i] - kCy[i] * S::RX];
+#pragma unroll
+            for (int i = 0; i < Q; ++i)
+                if (kCz[i] == 1) {
+                    now[tensor_slot(i)] = later[k];
+                    later[k++] = rd[i * R - kCx[i] - kCy[i] * S::RX];
+                }
+            if (kScalar) {
+#pragma unroll
+                for (int i = 0; i < 5; ++i) gnow[i] = rd[(Q + i) * R - kSx[i] - kSy[i] * S::RX];
+                gnow[5] = glater;
+                glater = rd[(Q + 5) * R];
+            }
+        }
+    }
+}
+
+// Rows per tile and planes per workgroup.  The workgroups run in rounds of
+// kPerCu per CU, each computes two planes more than it outputs, and a plane
+// takes its first- and second-step waves per SIMD (whole waves where one
+// workgroup has the CU, half a wave for the barriers).  Measured at 256^3:
+// 64 x 8 tiles of 128 planes (256 workgroups) 486 us per step, 64 x 13 of 86
+// planes (240) 500, 64 x 11 of 32 planes (768) 513; at 192^3 64 x 12 of 39
+// planes 207, 64 x 7 of 64 planes 221.
+template <int TX, int TY, int kPerCu>
+static void plan_tiles(PairArgs& a)
+{
+    const int64_t slots = 256 * kPerCu;
+    a.ntx = (a.nx + TX - 1) / TX;
+    double best = 1e300;
+    const int nt0 = (a.ny + TY - 1) / TY;
+    for (int nty = nt0; nty <= 2 * nt0 && nty <= nt0 + 16 && nty <= a.ny; ++nty) {
+        const int ty = (a.ny + nty - 1) / nty;
+        const int64_t tiles = (int64_t)a.ntx * ((a.ny + ty - 1) / ty);
+        const int w1 = ((ty + 2) * (TX + 2) + 63) / 64, w2 = (ty * TX + 63) / 64;
+        const double waves = kPerCu == 1 ? (w1 + 3) / 4 + (w2 + 3) / 4 : kPerCu * (w1 + w2) / 4.0;
+        const int64_t r0 = (tiles + slots - 1) / slots;
+        for (int64_t r = r0; r < r0 + 4; ++r) {
+            const int64_t chunks = std::min<int64_t>(a.nz, r * slots / tiles);
+            const int cz = (int)((a.nz + chunks - 1) / chunks);
+            const int64_t blocks = tiles * ((a.nz + cz - 1) / cz);
+            const double cost = (double)((blocks + slots - 1) / slots) * (cz + 2.5) * (waves + 0.5);
+            if (cost < best) {
+                best = cost;
+                a.nty = (a.ny + ty - 1) / ty;
+                a.ty = ty;
+                a.cz = cz;
+            }
+        }
+    }
+}
+
+template <bool kForce, bool kScalar, int TX, int TY, int kWaves, int kPerCu>
+static void launch_pair(PairArgs a, hipStream_t st)
+{
+    plan_tiles<TX, TY, kPerCu>(a);
+    const int64_t blocks = (int64_t)a.ntx * a.nty * ((a.nz + a.cz - 1) / a.cz);
+    const int threads = (std::max((a.ty + 2) * (TX + 2), a.ty * TX) + 63) / 64 * 64;
+    hipLaunchKernelGGL((k_step_pair<kForce, kScalar, TX, TY, kWaves, kPerCu>), dim3((unsigned)blocks),
+                       dim3((unsigned)threads), 0, st, a);
+}
+
+static PairArgs pair_args(const cslbm_level* L, const void* fin, void* fout, const float* gin, float* gout)
+{
+    PairArgs a;
+    a.f = static_cast<const float*>(fin);
+    a.fo = static_cast<float*>(fout);
+    a.g = gin;
+    a.go = gout;
+    a.force = L->force;
+    a.nx = L->nx;
+    a.ny = L->ny;
+    a.nz = L->nz;
+    a.ntx = a.nty = a.ty = a.cz = 1;
+    a.plane = L->plane;
+    a.r = make_rates(L->p);
+    a.beta = (float)L->p.beta;
+    a.s_ref = (float)L->p.s_ref;
+    a.inv_tau_s = gin ? (float)(1.0 / L->p.tau_s) : 0.0f;
+    return a;
+}
+
+// Tiles 64 cells wide, or 32 where the rows are multiples of half a cache
+// line and 64 would leave more lanes past the row's end (96^3: 27 against 30
+// us per step; 224^3: 322 against 362).  With other row lengths a 32-wide
+// tile writes every line in parts (181x118x77: 70 against 54 us).
+static bool narrow_tiles(const cslbm_level* L)
+{
+    const int w32 = (L->nx + 31) / 32 * 32, w64 = (L->nx + 63) / 64 * 64;
+    return L->nx <= 32 || (L->nx % 16 == 0 && w32 < w64);
+}
+
+// Levels whose pairs of steps run faster fused: fully periodic FP32 boxes
+// without flags or gradient mode, with enough cells to fill the CUs with
+// tiles (cells times the used part of the tiles' width; 64^3: 11.8 us per
+// step against 12.3; 72^3, 64-wide tiles half empty: 23 against 21.7) and a
+// few rows and planes for the halo to stay small.  Lane offsets in a plane
+// are 32-bit bytes.
+bool step_pair_applies(const cslbm_level* L)
+{
+    if (L->storage != CSLBM_F32 || L->flags || L->brick_table || (L->periodic & 7) != 7 ||
+        L->p.grad_mode != 0)
+        return false;
+    if (L->ny < 8 || L->nz < 8 || (int64_t)L->nx * L->ny >= (1 << 30)) return false;
+    const int tx = narrow_tiles(L) ? 32 : 64;
+    const double used = (double)L->nx / ((L->nx + tx - 1) / tx * tx);
+    return (double)cells_of(L) * used >= (double)(1 << 18);
+}
+
+int launch_step_pair(const cslbm_level* L, const void* fin, void* fout, const float* gin, float* gout,
+                     hipStream_t stream)
+{
+    const PairArgs a = pair_args(L, fin, fout, gin, gout);
+    const bool narrow = narrow_tiles(L);
+    // with the scalar three waves per SIMD (154-167 VGPRs; at four it spills)
+    if (gin && L->force) {
+        if (narrow)
+            launch_pair<true, true, 32, 16, 3, 1>(a, stream);
+        else
+            launch_pair<true, true, 64, 9, 3, 1>(a, stream);
+    } else if (gin) {
+        if (narrow)
+            launch_pair<false, true, 32, 16, 3, 1>(a, stream);
+        else
+            launch_pair<false, true, 64, 9, 3, 1>(a, stream);
+    } else if (L->force) {
+        if (narrow)
+            launch_pair<true, false, 32, 16, 3, 1>(a, stream);
+        else
+            launch_pair<true, false, 64, 9, 3, 1>(a, stream);
+    } else {
+        if (narrow)
+            launch_pair<false, false, 32, 13, 4, 2>(a, stream);
+        else
+            launch_pair<false, false, 64, 13, 4, 1>(a, stream);
+    }
+    return check_launch("k_step_pair");
+}
+
+}  // namespace cslbm
