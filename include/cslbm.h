@@ -370,7 +370,7 @@ typedef struct cslbm_scale {
                                            offsets, 0 first, n_post[j] last, at
                                            most 256 entries a run; a run outside
                                            these bounds is clipped to them).  When
-                                           both scales are dense boxes, scale i
+                                           scale i
                                            has no periodic axis and scale j's
                                            cells are not all lattice points of
                                            scale i, each run is mapped by one
@@ -393,8 +393,7 @@ typedef struct cslbm_scale {
                                            a run that starts among the x-face
                                            entries of one plane must hold only
                                            entries of that plane, or its
-                                           targets become NaN).  When this
-                                           scale and its parent are dense boxes,
+                                           targets become NaN).  When
                                            the parent has no periodic axis and
                                            this scale's cells are not all
                                            parent lattice points, the prior-

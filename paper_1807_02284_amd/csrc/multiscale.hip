@@ -419,8 +419,8 @@ int launch_exchange(const cslbm_level* src, const void* fA, const void* fB, cons
 {
     if (n_cells == 0) return CSLBM_OK;
     ExchArgs a = exchange_args(src, fA, fB, gA, gB, w, dst, f_out, g_out, cells, n_cells);
-    const bool tiled = runs && n_runs > 0 && !(w > 0.0 && w < 1.0) && !a.sb.table && !a.db.table &&
-                       a.speriodic == 0 && !nodes_coincide(src, dst);
+    const bool tiled = runs && n_runs > 0 && !(w > 0.0 && w < 1.0) && a.speriodic == 0 &&
+                       !nodes_coincide(src, dst);
     if (!tiled) return launch_exchange_args(a, src, dst, w, stream);
     return launch_tiled(a, src, dst, w, runs, n_runs, false, stream);
 }
@@ -598,13 +598,12 @@ int prior_stage(const cslbm_scale& sc, const cslbm_level* P, const void* A, cons
 }
 
 // The ghost shell's entries after its x faces go in patch runs through LDS
-// (cslbm_scale.ghost_tiles): dense boxes, no periodic parent axis, targets
-// off the parent's lattice points.
+// (cslbm_scale.ghost_tiles): no periodic parent axis, targets off the
+// parent's lattice points.
 static bool shell_tiled(const cslbm_scale& sc, const cslbm_level* P)
 {
     const cslbm_level* L = &sc.level;
-    return sc.ghost_tiles && sc.n_ghost_tiles > 0 && !P->brick_table && !L->brick_table &&
-           P->periodic == 0 && !nodes_coincide(P, L);
+    return sc.ghost_tiles && sc.n_ghost_tiles > 0 && P->periodic == 0 && !nodes_coincide(P, L);
 }
 
 int prior_map(const cslbm_scale& sc, bool staged, const cslbm_level* P, const void* A, const void* B,

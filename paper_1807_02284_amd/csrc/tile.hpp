@@ -2,8 +2,9 @@
 // (section "Spatial scale mapping"), shared by the tiled post-mapping and
 // its adjoint.
 //
-// Dense source and destination, no periodic source axis, targets off the
-// source lattice points.  One workgroup takes one run of the target list
+// No periodic source axis, targets off the source lattice points; either side
+// may be stored in bricks (a box cell whose brick is not stored is never a
+// corner of weight and loads storage cell 0).  One workgroup takes one run of the target list
 // (the host groups neighbouring cells of the destination into runs of at
 // most 256: a tile of a few rows).  The source cells the run's stencils
 // reach form a small box (a 32 x 8 x 1 tile at spacing ratio 4/3 reaches at
@@ -186,7 +187,8 @@ __device__ __forceinline__ bool tile_interp(const ExchArgs& a, const int32_t* ru
             const float wt = corner_weight(T.t, corner);
             const int cx = corner & 1 ? T.hi[0] : T.lo[0], cy = corner & 2 ? T.hi[1] : T.lo[1];
             const int cz = corner & 4 ? T.hi[2] : T.lo[2];
-            const int64_t sc = cx + (int64_t)n[0] * (cy + (int64_t)n[1] * cz);
+            const int64_t sc = a.sb.table ? source_cell(a, cx, cy, cz)
+                                          : cx + (int64_t)n[0] * (cy + (int64_t)n[1] * cz);
 #pragma unroll
             for (int i = 0; i < Q; ++i) {
                 const float hA = Io<Ts>::ld(fA + i * P + sc);
@@ -210,13 +212,14 @@ __device__ __forceinline__ bool tile_interp(const ExchArgs& a, const int32_t* ru
         return true;
     }
     // source offsets of this thread's box elements (the same in every plane)
-    const int64_t origin = x0 + (int64_t)n[0] * (y0 + (int64_t)n[1] * z0);
+    const bool sbrick = a.sb.table != nullptr;
+    const int64_t origin = sbrick ? 0 : x0 + (int64_t)n[0] * (y0 + (int64_t)n[1] * z0);
     int eoff[kLoads];
 #pragma unroll
     for (int k = 0; k < kLoads; ++k) {
         const int e = min(tid + 256 * k, V - 1);
         const int ex = e % bx, ey = (e / bx) % by, ez = e / (bx * by);
-        eoff[k] = ex + n[0] * (ey + n[1] * ez);
+        eoff[k] = sbrick ? (int)source_cell(a, x0 + ex, y0 + ey, z0 + ez) : ex + n[0] * (ey + n[1] * ez);
     }
     int cl[8];
     float wt[8];
