@@ -10,18 +10,21 @@
 // those with c_z = -1 complete the output plane below, those with c_z = 0 and
 // +1 wait in 27 registers for the planes to come.  A pair of steps reads the
 // state once and writes it once; what it pays is the first step of the
-// halo cells (a tile's perimeter, and two planes per workgroup).  One plane
-// of LDS per workgroup, two barriers per plane.
+// halo cells (a tile's perimeter, and two planes per workgroup).
 //
-// What bounds it: at 256^3 the VALU is busy about 70 % of the time and HBM
-// moves 4.1 TB/s, so neither alone; the loads of the next plane are in
-// flight during the second step only.  Fetching earlier (before the barrier,
-// or before the first step) needs 27 more registers: three waves per SIMD or
-// spills, both slower (487 -> 530-580 us per step at 256^3).  Per step,
-// pair against k_step: 486 / 642 us at 256^3, 53 / 82 us at 128^3, 54 /
-// 105 us at 181x118x77 (rows off the cache lines); with force and scalar 84 /
-// 108 us at 128^3.  binary16 levels stay with k_step, which the VALU already
-// limits.
+// Two planes of LDS where they fit (without the scalar): one barrier a plane,
+// and waves may run a plane's first step while others are at the second step
+// of the plane before.  One plane and two barriers: 424 -> 457 us per step at
+// 256^3.  The next plane's loads are issued before the barrier, as soon as
+// the plane in the registers is in LDS (after it: 457 -> 490 us); earlier
+// they need 27 more registers, which spill at four waves per SIMD, and at three
+// were slower (530-580 us).
+//
+// What bounds it: VALU issue, busy 82 % of the time at 256^3; HBM moves
+// 4.6 TB/s.  Per step, pair against k_step: 424 / 642 us at 256^3, 58 / 82 us
+// at 128^3, 61 / 105 us at 181x118x77 (rows off the cache lines), 28 / 39 us
+// at 96^3; with force and scalar 77 / 108 us at 128^3.  binary16 levels stay
+// with k_step: it already issues VALU instructions 87 % of the time.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -79,13 +82,15 @@ struct PlaneWalk {
     }
 };
 
-template <bool kForce, bool kScalar, int TX, int TY, int kWaves, int kPerCu>
+template <bool kForce, bool kScalar, int TX, int TY, int kWaves>
 __global__ void __launch_bounds__((PairShape<TX, TY>::kThreads))
     __attribute__((amdgpu_waves_per_eu(kWaves))) k_step_pair(const PairArgs a)
 {
     using S = PairShape<TX, TY>;
     constexpr int R = S::kRegion;
-    __shared__ float lds[(kScalar ? Q + QS : Q) * R];
+    constexpr int kPlane = (kScalar ? Q + QS : Q) * R;   // floats of a first-step plane
+    constexpr bool kTwo = 2 * kPlane * sizeof(float) <= 160 * 1024;
+    __shared__ float lds[kPlane * (kTwo ? 2 : 1)];
 
     const int nx = a.nx, ny = a.ny, nz = a.nz;
     const int64_t nxy = (int64_t)nx * ny;
@@ -103,16 +108,14 @@ __global__ void __launch_bounds__((PairShape<TX, TY>::kThreads))
     const int y = ((by * a.ty - 1 + ry) % ny + ny) % ny;
     const int xs[3] = {x == nx - 1 ? 0 : x + 1, x, x == 0 ? nx - 1 : x - 1};
     const int ys[3] = {(y == ny - 1 ? 0 : y + 1) * nx, y * nx, (y == 0 ? ny - 1 : y - 1) * nx};
-    // second-step cell.  With two workgroups on a CU, every second round of
-    // 256 workgroups leaves its first waves idle instead of its last, so
-    // that the two leave different SIMDs idle
-    const int t2 = t - (kPerCu == 2 && ((blockIdx.x >> 8) & 1) ? (int)blockDim.x - ((a.ty * TX + 63) & ~63) : 0);
-    const int ox = t2 & (TX - 1), oy = t2 >= 0 ? t2 / TX : a.ty;
+    // second-step cell
+    const int ox = t & (TX - 1), oy = t / TX;
     const int X = bx * TX + ox, Y = by * a.ty + oy;
     const bool out = oy < a.ty && X < nx && Y < ny;
     const uint32_t ocell = (uint32_t)(X + nx * Y) * 4u;
-    float* const wr = lds + t;
-    const float* const rd = lds + (oy + 1) * S::RX + ox + 1;
+    float* wr = lds + t;
+    const float* rd = lds + (oy + 1) * S::RX + ox + 1;
+    int other = kPlane;   // distance to the other plane's buffer
     const int z0 = bz * a.cz, z1 = min(z0 + a.cz, nz);
 
     float pre[27], gpre[QS], fpre[3];   // first-step cell: pulled, then collided
@@ -197,7 +200,7 @@ __global__ void __launch_bounds__((PairShape<TX, TY>::kThreads))
 #pragma unroll
             for (int d = 0; d < 3; ++d) F1[d] = fpre[d];
         collide(pre, gpre, F1);
-        __syncthreads();   // the previous plane has been read
+        if (!kTwo) __syncthreads();   // the previous plane has been read
         if (in_region) {
 #pragma unroll
             for (int i = 0; i < Q; ++i) wr[i * R] = pre[tensor_slot(i)];
@@ -205,10 +208,10 @@ __global__ void __launch_bounds__((PairShape<TX, TY>::kThreads))
 #pragma unroll
                 for (int i = 0; i < QS; ++i) wr[(Q + i) * R] = gpre[i];
         }
-        __syncthreads();
         // without a branch: a conditional fetch keeps both versions of the
         // registers (past the last plane it reloads that plane)
         fetch(min(p + 1, z1));
+        __syncthreads();
         // second step on output plane p - 1
         const bool store = out && p > z0;
         if (store) {
@@ -264,20 +267,24 @@ __global__ void __launch_bounds__((PairShape<TX, TY>::kThreads))
                 glater = rd[(Q + 5) * R];
             }
         }
+        if (kTwo) {
+            wr += other;
+            rd += other;
+            other = -other;
+        }
     }
 }
 
-// Rows per tile and planes per workgroup.  The workgroups run in rounds of
-// kPerCu per CU, each computes two planes more than it outputs, and a plane
-// takes its first- and second-step waves per SIMD (whole waves where one
-// workgroup has the CU, half a wave for the barriers).  Measured at 256^3:
-// 64 x 8 tiles of 128 planes (256 workgroups) 486 us per step, 64 x 13 of 86
-// planes (240) 500, 64 x 11 of 32 planes (768) 513; at 192^3 64 x 12 of 39
-// planes 207, 64 x 7 of 64 planes 221.
-template <int TX, int TY, int kPerCu>
+// Rows per tile and planes per workgroup.  One workgroup runs on a CU at a
+// time; the workgroups run in rounds of 256, each computes two planes more
+// than it outputs, and a plane takes its first- and second-step waves per SIMD
+// and half a wave for the barrier.  Measured at 256^3 (one LDS plane): 64 x 8
+// tiles of 128 planes (256 workgroups) 486 us per step, 64 x 13 of 86 planes
+// (240) 500, 64 x 11 of 32 planes (768) 513.
+template <int TX, int TY>
 static void plan_tiles(PairArgs& a)
 {
-    const int64_t slots = 256 * kPerCu;
+    constexpr int64_t slots = 256;
     a.ntx = (a.nx + TX - 1) / TX;
     double best = 1e300;
     const int nt0 = (a.ny + TY - 1) / TY;
@@ -285,13 +292,13 @@ static void plan_tiles(PairArgs& a)
         const int ty = (a.ny + nty - 1) / nty;
         const int64_t tiles = (int64_t)a.ntx * ((a.ny + ty - 1) / ty);
         const int w1 = ((ty + 2) * (TX + 2) + 63) / 64, w2 = (ty * TX + 63) / 64;
-        const double waves = kPerCu == 1 ? (w1 + 3) / 4 + (w2 + 3) / 4 : kPerCu * (w1 + w2) / 4.0;
+        const double waves = (w1 + 3) / 4 + (w2 + 3) / 4 + 0.5;
         const int64_t r0 = (tiles + slots - 1) / slots;
         for (int64_t r = r0; r < r0 + 4; ++r) {
             const int64_t chunks = std::min<int64_t>(a.nz, r * slots / tiles);
             const int cz = (int)((a.nz + chunks - 1) / chunks);
             const int64_t blocks = tiles * ((a.nz + cz - 1) / cz);
-            const double cost = (double)((blocks + slots - 1) / slots) * (cz + 2.5) * (waves + 0.5);
+            const double cost = (double)((blocks + slots - 1) / slots) * (cz + 2.5) * waves;
             if (cost < best) {
                 best = cost;
                 a.nty = (a.ny + ty - 1) / ty;
@@ -302,13 +309,13 @@ static void plan_tiles(PairArgs& a)
     }
 }
 
-template <bool kForce, bool kScalar, int TX, int TY, int kWaves, int kPerCu>
+template <bool kForce, bool kScalar, int TX, int TY, int kWaves>
 static void launch_pair(PairArgs a, hipStream_t st)
 {
-    plan_tiles<TX, TY, kPerCu>(a);
+    plan_tiles<TX, TY>(a);
     const int64_t blocks = (int64_t)a.ntx * a.nty * ((a.nz + a.cz - 1) / a.cz);
     const int threads = (std::max((a.ty + 2) * (TX + 2), a.ty * TX) + 63) / 64 * 64;
-    hipLaunchKernelGGL((k_step_pair<kForce, kScalar, TX, TY, kWaves, kPerCu>), dim3((unsigned)blocks),
+    hipLaunchKernelGGL((k_step_pair<kForce, kScalar, TX, TY, kWaves>), dim3((unsigned)blocks),
                        dim3((unsigned)threads), 0, st, a);
 }
 
@@ -333,9 +340,9 @@ static PairArgs pair_args(const cslbm_level* L, const void* fin, void* fout, con
 }
 
 // Tiles 64 cells wide, or 32 where the rows are multiples of half a cache
-// line and 64 would leave more lanes past the row's end (96^3: 27 against 30
-// us per step; 224^3: 322 against 362).  With other row lengths a 32-wide
-// tile writes every line in parts (181x118x77: 70 against 54 us).
+// line and 64 would leave more lanes past the row's end (96^3: 27.5 against
+// 35 us per step).  With other row lengths a 32-wide tile writes every line in
+// parts (181x118x77: 70 against 54 us, one LDS plane).
 static bool narrow_tiles(const cslbm_level* L)
 {
     const int w32 = (L->nx + 31) / 32 * 32, w64 = (L->nx + 63) / 64 * 64;
@@ -343,11 +350,12 @@ static bool narrow_tiles(const cslbm_level* L)
 }
 
 // Levels whose pairs of steps run faster fused: fully periodic FP32 boxes
-// without flags or gradient mode, with enough cells to fill the CUs with
-// tiles (cells times the used part of the tiles' width; 64^3: 11.8 us per
-// step against 12.3; 72^3, 64-wide tiles half empty: 23 against 21.7) and a
-// few rows and planes for the halo to stay small.  Lane offsets in a plane
-// are 32-bit bytes.
+// without flags or gradient mode, with enough cells to give every CU a tile
+// of some planes (cells times the used part of the tiles' width; 64^3: 12.8
+// us per step against 12.1 single; 64x64x128: 17.5 against 21.8; 72^3, tiles
+// half empty: 21.9 against 21.7) and a few rows and planes for the halo to
+// stay small (288x288x8: 25 against 30; 256x8x150: 15.1 against 15.7).  Lane
+// offsets in a plane are 32-bit bytes.
 bool step_pair_applies(const cslbm_level* L)
 {
     if (L->storage != CSLBM_F32 || L->flags || L->brick_table || (L->periodic & 7) != 7 ||
@@ -356,7 +364,7 @@ bool step_pair_applies(const cslbm_level* L)
     if (L->ny < 8 || L->nz < 8 || (int64_t)L->nx * L->ny >= (1 << 30)) return false;
     const int tx = narrow_tiles(L) ? 32 : 64;
     const double used = (double)L->nx / ((L->nx + tx - 1) / tx * tx);
-    return (double)cells_of(L) * used >= (double)(1 << 18);
+    return (double)cells_of(L) * used > (double)(1 << 18);
 }
 
 int launch_step_pair(const cslbm_level* L, const void* fin, void* fout, const float* gin, float* gout,
@@ -364,27 +372,27 @@ int launch_step_pair(const cslbm_level* L, const void* fin, void* fout, const fl
 {
     const PairArgs a = pair_args(L, fin, fout, gin, gout);
     const bool narrow = narrow_tiles(L);
-    // with the scalar three waves per SIMD (154-167 VGPRs; at four it spills)
+    // twelve waves, three per SIMD (the scalar takes 154-167 VGPRs)
     if (gin && L->force) {
         if (narrow)
-            launch_pair<true, true, 32, 16, 3, 1>(a, stream);
+            launch_pair<true, true, 32, 16, 3>(a, stream);
         else
-            launch_pair<true, true, 64, 9, 3, 1>(a, stream);
+            launch_pair<true, true, 64, 9, 3>(a, stream);
     } else if (gin) {
         if (narrow)
-            launch_pair<false, true, 32, 16, 3, 1>(a, stream);
+            launch_pair<false, true, 32, 16, 3>(a, stream);
         else
-            launch_pair<false, true, 64, 9, 3, 1>(a, stream);
+            launch_pair<false, true, 64, 9, 3>(a, stream);
     } else if (L->force) {
         if (narrow)
-            launch_pair<true, false, 32, 16, 3, 1>(a, stream);
+            launch_pair<true, false, 32, 20, 3>(a, stream);
         else
-            launch_pair<true, false, 64, 9, 3, 1>(a, stream);
+            launch_pair<true, false, 64, 9, 3>(a, stream);
     } else {
         if (narrow)
-            launch_pair<false, false, 32, 13, 4, 2>(a, stream);
+            launch_pair<false, false, 32, 20, 3>(a, stream);
         else
-            launch_pair<false, false, 64, 13, 4, 1>(a, stream);
+            launch_pair<false, false, 64, 9, 3>(a, stream);
     }
     return check_launch("k_step_pair");
 }
