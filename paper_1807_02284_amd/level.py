@@ -43,8 +43,11 @@ class Params:
 
 
 def _stream_handle(stream=None) -> int:
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return int(s.cuda_stream)
+    if stream is None:
+        # the current stream of the current device as torch keeps it; making
+        # the Stream object first takes 2.9 us of a 9 us step call
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return int(stream.cuda_stream)
 
 
 def _dev_ptr(t: torch.Tensor | None):
