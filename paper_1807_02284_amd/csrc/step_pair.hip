@@ -10,7 +10,8 @@
 // those with c_z = -1 complete the output plane below, those with c_z = 0 and
 // +1 wait in 27 registers for the planes to come.  A pair of steps reads the
 // state once and writes it once; what it pays is the first step of the
-// halo cells (a tile's perimeter, and two planes per workgroup).
+// halo cells (a tile's perimeter, and two planes per workgroup).  Small levels
+// take k_step_pair_box below.
 //
 // Two planes of LDS where they fit (without the scalar): one barrier a plane,
 // and waves may run a plane's first step while others are at the second step
@@ -81,6 +82,26 @@ struct PlaneWalk {
         return (GlobalFloat*)(b + off);
     }
 };
+
+// the cell update of k_step on pulled populations
+template <bool kScalar>
+__device__ __forceinline__ void collide_pulled(const PairArgs& a, float (&v)[27], float (&gv)[QS],
+                                               const float (&F)[3])
+{
+    float s = 0.0f;
+    float Fz = F[2];
+    if (kScalar) {
+        s = (gv[0] + (gv[1] + gv[2])) + ((gv[3] + gv[4]) + (gv[5] + gv[6]));
+        Fz += a.beta * (s - a.s_ref);
+    }
+    const CellMacro mc = cm_collide(v, a.r, F[0], F[1], Fz);
+    if (kScalar)
+#pragma unroll
+        for (int i = 0; i < QS; ++i) {
+            const float ge = scalar_eq(i, s, mc.ux, mc.uy, mc.uz);
+            gv[i] = gv[i] - (gv[i] - ge) * a.inv_tau_s;
+        }
+}
 
 template <bool kForce, bool kScalar, int TX, int TY, int kWaves>
 __global__ void __launch_bounds__((PairShape<TX, TY>::kThreads))
@@ -164,23 +185,6 @@ __global__ void __launch_bounds__((PairShape<TX, TY>::kThreads))
                          "v"(gpre[5]), "v"(gpre[6]));
         if (kForce) asm volatile("" : : "v"(fpre[0]), "v"(fpre[1]), "v"(fpre[2]));
     };
-    // the cell update of k_step on pulled populations
-    auto collide = [&](float (&v)[27], float (&gv)[QS], const float (&F)[3]) {
-        float s = 0.0f;
-        float Fz = F[2];
-        if (kScalar) {
-            s = (gv[0] + (gv[1] + gv[2])) + ((gv[3] + gv[4]) + (gv[5] + gv[6]));
-            Fz += a.beta * (s - a.s_ref);
-        }
-        const CellMacro mc = cm_collide(v, a.r, F[0], F[1], Fz);
-        if (kScalar)
-#pragma unroll
-            for (int i = 0; i < QS; ++i) {
-                const float ge = scalar_eq(i, s, mc.ux, mc.uy, mc.uz);
-                gv[i] = gv[i] - (gv[i] - ge) * a.inv_tau_s;
-            }
-    };
-
     // second-step populations gathered so far.  now: output plane p - 1 (those
     // with c_z = +1 and 0 already read); later: output plane p (c_z = +1)
     float now[27], later[9], gnow[QS], glater = 0.0f;
@@ -199,7 +203,7 @@ __global__ void __launch_bounds__((PairShape<TX, TY>::kThreads))
         if (kForce)
 #pragma unroll
             for (int d = 0; d < 3; ++d) F1[d] = fpre[d];
-        collide(pre, gpre, F1);
+        collide_pulled<kScalar>(a, pre, gpre, F1);
         if (!kTwo) __syncthreads();   // the previous plane has been read
         if (in_region) {
 #pragma unroll
@@ -228,7 +232,7 @@ __global__ void __launch_bounds__((PairShape<TX, TY>::kThreads))
                     w.next();
                 }
             }
-            collide(now, gnow, F2);
+            collide_pulled<kScalar>(a, now, gnow, F2);
         }
         arrived();
         if (store) {
@@ -319,6 +323,130 @@ static void launch_pair(PairArgs a, hipStream_t st)
                        dim3((unsigned)threads), 0, st, a);
 }
 
+// The same pair for levels too small to march: one TX x TY x TZ tile per
+// workgroup, the first step on it and one cell around it (a thread per cell)
+// into LDS, one barrier, the second step from there.  What bounds a small
+// step is its launch and the round trip to memory (4.3-4.6 us at 16^3 and at
+// 32^3 alike); two and a half times the first step's arithmetic costs less
+// than a second trip.  Per step, pair against k_step: 3.6 / 4.6 us at 32^3,
+// 6.1 / 8.3 us at 48^3, 10.5 / 12.2 us at 64^3, 15.1 / 21.4 us at 72^3; with
+// scalar and force 4.2 / 4.8 us at 32^3, 20.5 / 26.9 us at 72^3.  Larger tiles
+// share more but leave SIMDs idle or hold one workgroup per CU: 8x8x8 at 32^3
+// 4.9 us, 8x8x4 4.1, 16x6x4 4.6; 4x4x4 at 64^3 17.5.
+template <int TX, int TY, int TZ>
+struct BoxShape {
+    static constexpr int RX = TX + 2, RY = TY + 2, RZ = TZ + 2;
+    static constexpr int kRegion = RX * RY * RZ;   // first-step cells
+    static constexpr int kThreads = (kRegion + 63) / 64 * 64;
+    static constexpr int kCells = TX * TY * TZ;
+};
+
+template <bool kForce, bool kScalar, int TX, int TY, int TZ>
+__global__ void __launch_bounds__((BoxShape<TX, TY, TZ>::kThreads)) k_step_pair_box(const PairArgs a)
+{
+    using S = BoxShape<TX, TY, TZ>;
+    constexpr int R = S::kRegion;
+    __shared__ float lds[(kScalar ? Q + QS : Q) * R];
+
+    const int nx = a.nx, ny = a.ny, nz = a.nz;
+    const int nxy = nx * ny;
+    const int blk = xcd_block(blockIdx.x, gridDim.x);
+    const int bx = blk % a.ntx, by = (blk / a.ntx) % a.nty, bz = blk / (a.ntx * a.nty);
+    const int t = threadIdx.x;
+    // first-step cell; the box is at least a tile long each way, so one period
+    // brings any of them inside
+    const int rx = t % S::RX, ry = t / S::RX % S::RY, rz = min(t / (S::RX * S::RY), S::RZ - 1);
+    auto wrap = [](int v, int n) { return v < 0 ? v + n : (v >= n ? v - n : v); };
+    const int x = wrap(bx * TX - 1 + rx, nx), y = wrap(by * TY - 1 + ry, ny), z = wrap(bz * TZ - 1 + rz, nz);
+    const int xs[3] = {x == nx - 1 ? 0 : x + 1, x, x == 0 ? nx - 1 : x - 1};
+    const int ys[3] = {(y == ny - 1 ? 0 : y + 1) * nx, y * nx, (y == 0 ? ny - 1 : y - 1) * nx};
+    const int zs[3] = {(z == nz - 1 ? 0 : z + 1) * nxy, z * nxy, (z == 0 ? nz - 1 : z - 1) * nxy};
+    // second-step cell
+    const int ox = t % TX, oy = t / TX % TY, oz = t / (TX * TY);
+    const int X = bx * TX + ox, Y = by * TY + oy, Z = bz * TZ + oz;
+    const bool out = t < S::kCells && X < nx && Y < ny && Z < nz;
+    const uint32_t ocell = (uint32_t)(X + nx * Y + nxy * Z) * 4u;
+
+    float v[27], g[QS], F1[3] = {0.0f, 0.0f, 0.0f}, F2[3] = {0.0f, 0.0f, 0.0f};
+    PlaneWalk w(a.plane);
+#pragma unroll
+    for (int i = 0; i < Q; ++i) {
+        v[tensor_slot(i)] = *w.lane(a.f, (uint32_t)(xs[kCx[i] + 1] + ys[kCy[i] + 1] + zs[kCz[i] + 1]) * 4u);
+        w.next();
+    }
+    if (kScalar) {
+        PlaneWalk wg(a.plane);
+#pragma unroll
+        for (int i = 0; i < QS; ++i) {
+            g[i] = *wg.lane(a.g, (uint32_t)(xs[kSx[i] + 1] + ys[kSy[i] + 1] + zs[kSz[i] + 1]) * 4u);
+            wg.next();
+        }
+    }
+    if (kForce) {
+        PlaneWalk wf(a.plane);
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            F1[d] = *wf.lane(a.force, (uint32_t)(xs[1] + ys[1] + zs[1]) * 4u);
+            if (out) F2[d] = *wf.lane(a.force, ocell);
+            wf.next();
+        }
+    }
+    collide_pulled<kScalar>(a, v, g, F1);
+    if (t < R) {
+#pragma unroll
+        for (int i = 0; i < Q; ++i) lds[i * R + t] = v[tensor_slot(i)];
+        if (kScalar)
+#pragma unroll
+            for (int i = 0; i < QS; ++i) lds[(Q + i) * R + t] = g[i];
+    }
+    __syncthreads();
+    if (!out) return;
+    const float* rd = lds + ((oz + 1) * S::RY + oy + 1) * S::RX + ox + 1;
+#pragma unroll
+    for (int i = 0; i < Q; ++i)
+        v[tensor_slot(i)] = rd[i * R - kCx[i] - kCy[i] * S::RX - kCz[i] * S::RX * S::RY];
+    if (kScalar)
+#pragma unroll
+        for (int i = 0; i < QS; ++i)
+            g[i] = rd[(Q + i) * R - kSx[i] - kSy[i] * S::RX - kSz[i] * S::RX * S::RY];
+    collide_pulled<kScalar>(a, v, g, F2);
+    PlaneWalk wo(a.plane);
+#pragma unroll
+    for (int i = 0; i < Q; ++i) {
+        *wo.lane(a.fo, ocell) = v[tensor_slot(i)];
+        wo.next();
+    }
+    if (kScalar) {
+        PlaneWalk wg(a.plane);
+#pragma unroll
+        for (int i = 0; i < QS; ++i) {
+            *wg.lane(a.go, ocell) = g[i];
+            wg.next();
+        }
+    }
+}
+
+template <bool kForce, bool kScalar, int TX, int TY, int TZ>
+static void launch_box(PairArgs a, hipStream_t st)
+{
+    a.ntx = (a.nx + TX - 1) / TX;
+    a.nty = (a.ny + TY - 1) / TY;
+    const int blocks = a.ntx * a.nty * ((a.nz + TZ - 1) / TZ);
+    hipLaunchKernelGGL((k_step_pair_box<kForce, kScalar, TX, TY, TZ>), dim3((unsigned)blocks),
+                       dim3((unsigned)BoxShape<TX, TY, TZ>::kThreads), 0, st, a);
+}
+
+template <bool kForce, bool kScalar>
+static void launch_box(const PairArgs& a, int tile, hipStream_t st)
+{
+    if (tile == 0)
+        launch_box<kForce, kScalar, 8, 4, 4>(a, st);
+    else if (tile == 1)
+        launch_box<kForce, kScalar, 8, 6, 4>(a, st);
+    else if constexpr (!kScalar)
+        launch_box<kForce, kScalar, 16, 4, 4>(a, st);
+}
+
 static PairArgs pair_args(const cslbm_level* L, const void* fin, void* fout, const float* gin, float* gout)
 {
     PairArgs a;
@@ -349,28 +477,83 @@ static bool narrow_tiles(const cslbm_level* L)
     return L->nx <= 32 || (L->nx % 16 == 0 && w32 < w64);
 }
 
-// Levels whose pairs of steps run faster fused: fully periodic FP32 boxes
-// without flags or gradient mode, with enough cells to give every CU a tile
-// of some planes (cells times the used part of the tiles' width; 64^3: 12.8
-// us per step against 12.1 single; 64x64x128: 17.5 against 21.8; 72^3, tiles
-// half empty: 21.9 against 21.7) and a few rows and planes for the halo to
-// stay small (288x288x8: 25 against 30; 256x8x150: 15.1 against 15.7).  Lane
-// offsets in a plane are 32-bit bytes.
-bool step_pair_applies(const cslbm_level* L)
+// Whether a pair marches along z: enough cells to give every CU a tile of
+// some planes (cells times the used part of the tiles' width; per step at
+// 64^3 12.8 us against 12.1 single, 64x64x128 16.8 against 21.6) and a few
+// rows and planes for the halo to stay small (288x288x8: 25 against 30;
+// 256x8x150: 15.1 against 15.7).  Lane offsets in a plane are 32-bit bytes.
+static bool marches(const cslbm_level* L)
 {
-    if (L->storage != CSLBM_F32 || L->flags || L->brick_table || (L->periodic & 7) != 7 ||
-        L->p.grad_mode != 0)
-        return false;
     if (L->ny < 8 || L->nz < 8 || (int64_t)L->nx * L->ny >= (1 << 30)) return false;
     const int tx = narrow_tiles(L) ? 32 : 64;
     const double used = (double)L->nx / ((L->nx + tx - 1) / tx * tx);
     return (double)cells_of(L) * used > (double)(1 << 18);
 }
 
+// The tile of k_step_pair_box for a level, -1 where two single steps are
+// faster or as fast.  Both sides are estimated in us from lines through the
+// measured times of 160 random boxes of 2k-600k cells: a pair costs a launch
+// and, on the CU that has most tiles, their first- and second-step waves; a
+// step a launch, its 256-thread blocks (more where rows are shorter than a few
+// 32-byte sectors) and the cells that outgrow the L2s.  Which side wins
+// changes with how the tiles fill the last round over 256 CUs (with scalar
+// and force 66x62x19: 8.1 us per step against 7.8 single; 45x23x77: 7.0
+// against 8.2), so a limit on the cells alone would not do.
+static int box_tile(const cslbm_level* L)
+{
+    constexpr int tx[3] = {8, 8, 16}, ty[3] = {4, 6, 4}, tz = 4;
+    constexpr double wave_us[2][3] = {{0.33, 0.285, 0.265}, {0.44, 0.36, 0.0}};
+    const int64_t cells = cells_of(L);
+    const bool scalar = L->g != nullptr;
+    if (cells > (1 << 19)) return -1;
+    const dim3 b = step_block(L->nx);
+    const double rounds = (double)((L->nx + b.x - 1) / b.x) * ((L->ny + b.y - 1) / b.y) * L->nz / 256.0;
+    const double spill = std::max((double)cells - (scalar ? 0.9e5 : 1.4e5), 0.0);
+    const double work = scalar ? 1.45 * rounds + 6e-5 * spill : 1.65 * rounds + 4e-5 * spill;
+    const double single = (scalar ? 3.5 : 3.8) + (L->nx < 24 ? 1.25 : 1.0) * work;
+    int tile = -1;
+    double best = 0.92 * 2.0 * std::max(single, 4.6);
+    for (int k = 0; k < (scalar ? 2 : 3); ++k) {
+        // one period brings a halo cell inside
+        if (L->nx < tx[k] || L->ny < ty[k] || L->nz < tz) continue;
+        const int64_t blocks = (int64_t)((L->nx + tx[k] - 1) / tx[k]) * ((L->ny + ty[k] - 1) / ty[k]) *
+                               ((L->nz + tz - 1) / tz);
+        const int waves = ((tx[k] + 2) * (ty[k] + 2) * (tz + 2) + 63) / 64 + (tx[k] * ty[k] * tz + 63) / 64;
+        const double us = (scalar ? 5.2 : 4.8) + wave_us[scalar][k] * (double)((blocks + 255) / 256 * waves);
+        if (us < best) {
+            best = us;
+            tile = k;
+        }
+    }
+    return tile;
+}
+
+// Levels whose pairs of steps run faster fused: fully periodic FP32 boxes
+// without flags or gradient mode.
+bool step_pair_applies(const cslbm_level* L)
+{
+    if (L->storage != CSLBM_F32 || L->flags || L->brick_table || (L->periodic & 7) != 7 ||
+        L->p.grad_mode != 0)
+        return false;
+    return marches(L) || box_tile(L) >= 0;
+}
+
 int launch_step_pair(const cslbm_level* L, const void* fin, void* fout, const float* gin, float* gout,
                      hipStream_t stream)
 {
     const PairArgs a = pair_args(L, fin, fout, gin, gout);
+    if (!marches(L)) {
+        const int tile = box_tile(L);
+        if (gin && L->force)
+            launch_box<true, true>(a, tile, stream);
+        else if (gin)
+            launch_box<false, true>(a, tile, stream);
+        else if (L->force)
+            launch_box<true, false>(a, tile, stream);
+        else
+            launch_box<false, false>(a, tile, stream);
+        return check_launch("k_step_pair_box");
+    }
     const bool narrow = narrow_tiles(L);
     // twelve waves, three per SIMD (the scalar takes 154-167 VGPRs)
     if (gin && L->force) {
