@@ -21,8 +21,8 @@
 // they need 27 more registers, which spill at four waves per SIMD, and at three
 // were slower (530-580 us).
 //
-// What bounds it: VALU issue, busy 82 % of the time at 256^3; HBM moves
-// 4.6 TB/s.  Per step, pair against k_step: 424 / 642 us at 256^3, 58 / 82 us
+// What bounds it: VALU issue, busy 81 % of the time at 256^3; HBM moves
+// 4.5 TB/s.  Per step, pair against k_step: 424 / 642 us at 256^3, 58 / 82 us
 // at 128^3, 61 / 105 us at 181x118x77 (rows off the cache lines), 28 / 39 us
 // at 96^3; with force and scalar 77 / 108 us at 128^3.  binary16 levels stay
 // with k_step: it already issues VALU instructions 87 % of the time.
