@@ -283,7 +283,7 @@ __global__ void k_macro(const T* f, const float* g, const float* force, int64_t 
 // next is not among the three being read), and the output threads take their
 // differences there.  Against a velocity field written to temporary memory
 // and differenced by a second kernel: 490 / 556 us at 256^3 FP32, 331 / 390
-// binary16, 47 / 62 us at 128^3, 13 / 22 us at 48^3.  At 256^3 it is bound by
+// binary16, 47 / 62 us at 128^3, 13 / 19 us at 64^3.  At 256^3 it is bound by
 // the lines at the tiles' edges, which its two neighbours fetch as well (the
 // read-back of density and velocity alone takes 388 us); fetching a plane
 // ahead in registers, 5- or 13-row tiles and one or four workgroups per CU
@@ -303,6 +303,35 @@ struct VortArgs {
     float* speed;
 };
 
+// the cell an index of the tile's rim stands for: outside the box it wraps on
+// a periodic axis and repeats the face cell on the others (never read there)
+__device__ __forceinline__ int vort_cell(int i, int n, bool periodic)
+{
+    return periodic ? (i % n + n) % n : min(max(i, 0), n - 1);
+}
+
+// offsets of the two differenced points along an axis (0 at a face); the
+// distance between them is 1 or 2 cells, or 0 along a single cell
+__device__ __forceinline__ void vort_points(int i, int n, bool periodic, int& lo, int& hi)
+{
+    lo = !periodic && i == 0 ? 0 : 1;
+    hi = !periodic && i == n - 1 ? 0 : 1;
+}
+
+__device__ __forceinline__ float vort_slope(float hi, float lo, int h)
+{
+    return h > 0 ? (hi - lo) * (h == 1 ? 1.0f : 0.5f) : 0.0f;
+}
+
+// grad[a][b] = d u_a / d x_b and the cell's velocity, to cell c
+__device__ __forceinline__ void vort_store(const VortArgs& a, int64_t c, const float (&grad)[3][3],
+                                           float ux, float uy, float uz)
+{
+    const float wx = grad[2][1] - grad[1][2], wy = grad[0][2] - grad[2][0], wz = grad[1][0] - grad[0][1];
+    __builtin_nontemporal_store(sqrtf(wx * wx + wy * wy + wz * wz), a.out + c);
+    if (a.speed) __builtin_nontemporal_store(sqrtf(ux * ux + uy * uy + uz * uz), a.speed + c);
+}
+
 template <typename T>
 __global__ void __launch_bounds__((kVortRegion + 63) / 64 * 64) k_vorticity(const VortArgs a)
 {
@@ -314,33 +343,19 @@ __global__ void __launch_bounds__((kVortRegion + 63) / 64 * 64) k_vorticity(cons
     const int bx = blk % a.ntx, by = (blk / a.ntx) % a.nty, bz = blk / (a.ntx * a.nty);
     const int t = threadIdx.x;
     const bool in_region = t < kVortRegion;
-    // cell of this thread in the region; indices outside the box wrap on
-    // periodic axes and repeat the face cell on the others (never read there)
-    auto inside = [](int i, int n, bool periodic) {
-        return periodic ? (i % n + n) % n : min(max(i, 0), n - 1);
-    };
-    const int x = inside(bx * kVortTX - 1 + t % kVortRX, nx, a.periodic & 1);
-    const int y = inside(by * kVortTY - 1 + t / kVortRX, ny, a.periodic & 2);
+    const int x = vort_cell(bx * kVortTX - 1 + t % kVortRX, nx, a.periodic & 1);
+    const int y = vort_cell(by * kVortTY - 1 + t / kVortRX, ny, a.periodic & 2);
     const int ox = t % kVortTX, oy = t / kVortTX;
     const int X = bx * kVortTX + ox, Y = by * kVortTY + oy;
     const bool out = oy < kVortTY && X < nx && Y < ny;
     const int centre = (oy + 1) * kVortRX + ox + 1;
-    // offsets of the two differenced points along an axis (0 at a face); the
-    // distance between them is 1 or 2 cells, or 0 along a single cell
-    auto points = [](int i, int n, bool periodic, int& lo, int& hi) {
-        lo = !periodic && i == 0 ? 0 : 1;
-        hi = !periodic && i == n - 1 ? 0 : 1;
-    };
-    auto slope = [](float hi, float lo, int h) {
-        return h > 0 ? (hi - lo) * (h == 1 ? 1.0f : 0.5f) : 0.0f;
-    };
     int xlo, xhi, ylo, yhi;
-    points(X, nx, a.periodic & 1, xlo, xhi);
-    points(Y, ny, a.periodic & 2, ylo, yhi);
+    vort_points(X, nx, a.periodic & 1, xlo, xhi);
+    vort_points(Y, ny, a.periodic & 2, ylo, yhi);
     const int z0 = bz * a.cz, z1 = min(z0 + a.cz, nz);
     for (int p = z0 - 1; p <= z1; ++p) {
         if (in_region) {
-            const int64_t c = x + (int64_t)nx * y + nxy * inside(p, nz, a.periodic & 4);
+            const int64_t c = x + (int64_t)nx * y + nxy * vort_cell(p, nz, a.periodic & 4);
             float v[27];
 #pragma unroll
             for (int i = 0; i < Q; ++i) v[tensor_slot(i)] = Io<T>::ld(f + i * P + c);
@@ -353,25 +368,80 @@ __global__ void __launch_bounds__((kVortRegion + 63) / 64 * 64) k_vorticity(cons
         if (!out || p <= z0) continue;
         const int z = p - 1;
         int zlo, zhi;
-        points(z, nz, a.periodic & 4, zlo, zhi);
+        vort_points(z, nz, a.periodic & 4, zlo, zhi);
         const float (&here)[3][kVortRegion] = ring[z & 3];
         const float (&below)[3][kVortRegion] = ring[(z - zlo) & 3];
         const float (&above)[3][kVortRegion] = ring[(z + zhi) & 3];
-        float grad[3][3];   // grad[a][b] = d u_a / d x_b
+        float grad[3][3];
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
-            grad[k][0] = slope(here[k][centre + xhi], here[k][centre - xlo], xlo + xhi);
-            grad[k][1] = slope(here[k][centre + yhi * kVortRX], here[k][centre - ylo * kVortRX], ylo + yhi);
-            grad[k][2] = slope(above[k][centre], below[k][centre], zlo + zhi);
+            grad[k][0] = vort_slope(here[k][centre + xhi], here[k][centre - xlo], xlo + xhi);
+            grad[k][1] = vort_slope(here[k][centre + yhi * kVortRX], here[k][centre - ylo * kVortRX], ylo + yhi);
+            grad[k][2] = vort_slope(above[k][centre], below[k][centre], zlo + zhi);
         }
-        const float wx = grad[2][1] - grad[1][2], wy = grad[0][2] - grad[2][0], wz = grad[1][0] - grad[0][1];
-        const int64_t c = X + (int64_t)nx * Y + nxy * z;
-        __builtin_nontemporal_store(sqrtf(wx * wx + wy * wy + wz * wz), a.out + c);
-        if (a.speed) {
-            const float ux = here[0][centre], uy = here[1][centre], uz = here[2][centre];
-            __builtin_nontemporal_store(sqrtf(ux * ux + uy * uy + uz * uz), a.speed + c);
-        }
+        vort_store(a, X + (int64_t)nx * Y + nxy * z, grad, here[0][centre], here[1][centre], here[2][centre]);
     }
+}
+
+// The same for small boxes, whose walk along z would be a chain of memory round
+// trips with few workgroups: one tile per workgroup, every cell of it and of
+// one cell around it at once, one barrier.  Against the walk: 4.0 / 17.2 us at
+// 16^3, 4.1 / 13.2 us at 32^3, 5.7 / 13.1 us at 48x48x40; bound by the launch
+// and one round trip.
+template <typename T, int TX, int TY, int TZ>
+__global__ void __launch_bounds__(((TX + 2) * (TY + 2) * (TZ + 2) + 63) / 64 * 64)
+    k_vorticity_box(const VortArgs a)
+{
+    constexpr int RX = TX + 2, RY = TY + 2, RZ = TZ + 2, R = RX * RY * RZ;
+    __shared__ float u[3][R];
+    const int nx = a.nx, ny = a.ny, nz = a.nz;
+    const int64_t nxy = (int64_t)nx * ny;
+    const int blk = xcd_block(blockIdx.x, gridDim.x);
+    const int bx = blk % a.ntx, by = (blk / a.ntx) % a.nty, bz = blk / (a.ntx * a.nty);
+    const int t = threadIdx.x;
+    if (t < R) {
+        const int64_t c = vort_cell(bx * TX - 1 + t % RX, nx, a.periodic & 1) +
+                          (int64_t)nx * vort_cell(by * TY - 1 + t / RX % RY, ny, a.periodic & 2) +
+                          nxy * vort_cell(bz * TZ - 1 + t / (RX * RY), nz, a.periodic & 4);
+        const T* f = static_cast<const T*>(a.f);
+        float v[27];
+#pragma unroll
+        for (int i = 0; i < Q; ++i) v[tensor_slot(i)] = Io<T>::ld(f + i * a.plane + c);
+        float w[3];
+        velocity(v, a.g, a.force, a.plane, c, a.beta, a.s_ref, w);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) u[k][t] = w[k];
+    }
+    __syncthreads();
+    const int ox = t % TX, oy = t / TX % TY, oz = t / (TX * TY);
+    const int X = bx * TX + ox, Y = by * TY + oy, Z = bz * TZ + oz;
+    if (oz >= TZ || X >= nx || Y >= ny || Z >= nz) return;
+    const int centre = ((oz + 1) * RY + oy + 1) * RX + ox + 1;
+    int xlo, xhi, ylo, yhi, zlo, zhi;
+    vort_points(X, nx, a.periodic & 1, xlo, xhi);
+    vort_points(Y, ny, a.periodic & 2, ylo, yhi);
+    vort_points(Z, nz, a.periodic & 4, zlo, zhi);
+    float grad[3][3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        grad[k][0] = vort_slope(u[k][centre + xhi], u[k][centre - xlo], xlo + xhi);
+        grad[k][1] = vort_slope(u[k][centre + yhi * RX], u[k][centre - ylo * RX], ylo + yhi);
+        grad[k][2] = vort_slope(u[k][centre + zhi * RX * RY], u[k][centre - zlo * RX * RY], zlo + zhi);
+    }
+    vort_store(a, X + (int64_t)nx * Y + nxy * Z, grad, u[0][centre], u[1][centre], u[2][centre]);
+}
+
+template <int TX, int TY, int TZ>
+static void launch_vorticity_box(VortArgs a, bool half, hipStream_t st)
+{
+    a.ntx = (a.nx + TX - 1) / TX;
+    a.nty = (a.ny + TY - 1) / TY;
+    const dim3 grid((unsigned)((int64_t)a.ntx * a.nty * ((a.nz + TZ - 1) / TZ)));
+    const dim3 block(((TX + 2) * (TY + 2) * (TZ + 2) + 63) / 64 * 64);
+    if (half)
+        hipLaunchKernelGGL((k_vorticity_box<_Float16, TX, TY, TZ>), grid, block, 0, st, a);
+    else
+        hipLaunchKernelGGL((k_vorticity_box<float, TX, TY, TZ>), grid, block, 0, st, a);
 }
 
 // FP64 conservation: per-block partial sums (count, sum h, sum c h, sum g),
@@ -818,16 +888,33 @@ int cslbm_vorticity(const cslbm_level* L, float* omega, float* speed, hipStream_
     a.s_ref = (float)L->p.s_ref;
     a.out = omega;
     a.speed = speed;
+    // small boxes: the smallest tile that gives a CU one workgroup at most
+    // (48x48x40: 16x6x4 5.7 us, 16x4x4 6.9, 8x4x4 7.8), 16x4x4 for a few more;
+    // at 1024 of those the march is as fast (64^3: 13.1 against 13.4 us)
+    auto tiles_of = [&](int tx, int ty) {
+        return (int64_t)blocks_for(L->nx, tx) * blocks_for(L->ny, ty) * blocks_for(L->nz, 4);
+    };
+    const bool half = L->storage != CSLBM_F32;
+    const int64_t wide = tiles_of(16, 4);
+    if (wide <= 768) {
+        if (tiles_of(8, 4) <= 256)
+            launch_vorticity_box<8, 4, 4>(a, half, stream);
+        else if (wide > 256 && tiles_of(16, 6) <= 256)
+            launch_vorticity_box<16, 6, 4>(a, half, stream);
+        else
+            launch_vorticity_box<16, 4, 4>(a, half, stream);
+        return check_launch("k_vorticity_box");
+    }
     // two workgroups on every CU; a workgroup reads two planes more than it
     // writes, so it takes at least four where the box is small
     const int64_t tiles = (int64_t)a.ntx * a.nty;
     const int64_t chunks = std::max<int64_t>(1, std::min<int64_t>(512 / tiles, (L->nz + 3) / 4));
     a.cz = (int)((L->nz + chunks - 1) / chunks);
     const dim3 grid((unsigned)(tiles * ((L->nz + a.cz - 1) / a.cz))), block((kVortRegion + 63) / 64 * 64);
-    if (L->storage == CSLBM_F32)
-        hipLaunchKernelGGL(k_vorticity<float>, grid, block, 0, stream, a);
-    else
+    if (half)
         hipLaunchKernelGGL(k_vorticity<_Float16>, grid, block, 0, stream, a);
+    else
+        hipLaunchKernelGGL(k_vorticity<float>, grid, block, 0, stream, a);
     return check_launch("k_vorticity");
 }
 
