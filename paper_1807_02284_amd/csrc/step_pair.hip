@@ -482,11 +482,18 @@ static bool narrow_tiles(const cslbm_level* L)
 // 64^3 12.8 us against 12.1 single, 64x64x128 16.8 against 21.6) and a few
 // rows and planes for the halo to stay small (288x288x8: 25 against 30;
 // 256x8x150: 15.1 against 15.7).  Lane offsets in a plane are 32-bit bytes.
+// Up to 2^19 cells, where the small tiles were measured, those take rows that
+// leave much of the marching tiles empty (75x145x43: 22.4 us against 26.8;
+// 40x100x120: 19.9 against 23.9; 137x100x37: 23.8 against 25.5; but 95x64x80,
+// 74 % used, with scalar: 27.8 against 25.7).
+constexpr int64_t kBoxCells = 1 << 19;
+
 static bool marches(const cslbm_level* L)
 {
     if (L->ny < 8 || L->nz < 8 || (int64_t)L->nx * L->ny >= (1 << 30)) return false;
     const int tx = narrow_tiles(L) ? 32 : 64;
     const double used = (double)L->nx / ((L->nx + tx - 1) / tx * tx);
+    if (cells_of(L) <= kBoxCells && used < (L->nx > 64 ? 0.72 : 0.65)) return false;
     return (double)cells_of(L) * used > (double)(1 << 18);
 }
 
@@ -505,7 +512,7 @@ static int box_tile(const cslbm_level* L)
     constexpr double wave_us[2][3] = {{0.33, 0.285, 0.265}, {0.44, 0.36, 0.0}};
     const int64_t cells = cells_of(L);
     const bool scalar = L->g != nullptr;
-    if (cells > (1 << 19)) return -1;
+    if (cells > kBoxCells) return -1;
     const dim3 b = step_block(L->nx);
     const double rounds = (double)((L->nx + b.x - 1) / b.x) * ((L->ny + b.y - 1) / b.y) * L->nz / 256.0;
     const double spill = std::max((double)cells - (scalar ? 0.9e5 : 1.4e5), 0.0);
