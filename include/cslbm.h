@@ -243,6 +243,7 @@ int cslbm_get_populations(const cslbm_level* L, float* f, float* g, int32_t shif
  * swap L->f <-> L->f_next (and g) in *L.  After an even number of steps the
  * buffers are back in their original roles.  Calls of five and more steps on
  * fully periodic FP32 levels without flags may compute two steps per launch;
+ * the states are the same bit for bit, so a run may be split into calls at will,
  * the roles of the buffers are the same, and L->f_next holds the state before
  * the last step either way. */
 int cslbm_step(cslbm_level* L, int32_t n_steps, hipStream_t stream);

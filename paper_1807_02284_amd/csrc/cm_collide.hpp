@@ -202,7 +202,11 @@ __host__ __device__ __forceinline__ void from_moments(float (&v)[27], float ux, 
 }
 
 // D = k^eq(rho, u) - K(u) w for every moment, dr = rho - 1.  Order-1 entries
-// are u (k^eq vanishes, K(u) w gives -u).
+// are u (k^eq vanishes, K(u) w gives -u).  The sum of the three products of
+// squares is written as the fused operations it becomes: which of two products
+// with one use each is fused would follow their order, which differs from
+// kernel to kernel, and a pair of steps (step_pair.hip) is to give k_step's
+// bits.
 __host__ __device__ __forceinline__ void deviation_equilibrium(float (&d)[27], float dr, float X, float Y,
                                                       float Z)
 {
@@ -237,7 +241,7 @@ __host__ __device__ __forceinline__ void deviation_equilibrium(float (&d)[27], f
     d[kslot(2, 1, 2)] = Y * (ninth - dr * (X2 + Z2) * third + r16 * X2 * Z2);
     d[kslot(2, 2, 1)] = Z * (ninth - dr * (X2 + Y2) * third + r16 * X2 * Y2);
     d[kslot(2, 2, 2)] = dr * (1.0f / 27.0f) - (X2 + Y2 + Z2) * ninth +
-                        (2.0f * third + dr) * (X2 * Y2 + X2 * Z2 + Y2 * Z2) +
+                        (2.0f * third + dr) * __builtin_fmaf(Y2, Z2, __builtin_fmaf(X2, Y2, X2 * Z2)) +
                         (9.0f + 10.0f * dr) * X2 * Y2 * Z2;
 }
 
@@ -275,27 +279,45 @@ struct CellMacro {
     float rho, ux, uy, uz, G, phi;
 };
 
+// Density deviation, 1 / rho and momentum with half the force of a cell.
+struct CellMomentum {
+    float dr, inv_rho, px, py, pz;
+};
+
 // Central-moment collision of one cell, in place on shifted populations.
 // F is the body force (zero when absent): u = (j + F/2)/rho and the
 // order-one central moments receive +F (source (I - S/2) R with S_1..3 = 0).
 // active == false relaxes nothing (the transform pair is then an identity up
 // to rounding); kernels use it for lanes of non-fluid cells.  g_given >= 0
 // replaces the cell's own estimate of the gradient magnitude G.
-__host__ __device__ __forceinline__ CellMacro cm_collide(float (&v)[27], const Rates& r, float Fx, float Fy,
-                                               float Fz, bool active = true, float g_given = -1.0f)
+// In two halves, the transform to central moments and the rest: no product
+// formed in the first is an addend in the second (which forms the velocity
+// again), so a kernel that puts them in different basic blocks (the compiler
+// fuses multiplications into additions inside one) gets the same bits.
+__host__ __device__ __forceinline__ CellMomentum cm_collide_transform(float (&v)[27], float Fx, float Fy,
+                                                                      float Fz)
 {
     float dr, jx, jy, jz;
     xsweep_sums(v);
     moments_of_sums(v, dr, jx, jy, jz);
     const float rho = 1.0f + dr;
     const float inv_rho = rcp(rho);
-    const float ux = (jx + 0.5f * Fx) * inv_rho;
-    const float uy = (jy + 0.5f * Fy) * inv_rho;
-    const float uz = (jz + 0.5f * Fz) * inv_rho;
+    const float px = jx + 0.5f * Fx, py = jy + 0.5f * Fy, pz = jz + 0.5f * Fz;
+    const float ux = px * inv_rho, uy = py * inv_rho, uz = pz * inv_rho;
 
     xsweep_finish(v, ux);
     sweep_fwd<3, 1, 9>(v, uy);
     sweep_fwd<9, 1, 3>(v, uz);
+    return CellMomentum{dr, inv_rho, px, py, pz};
+}
+
+__host__ __device__ __forceinline__ CellMacro cm_collide_relax(float (&v)[27], const CellMomentum& m,
+                                                               const Rates& r, float Fx, float Fy, float Fz,
+                                                               bool active = true, float g_given = -1.0f)
+{
+    const float dr = m.dr, inv_rho = m.inv_rho;
+    const float ux = m.px * inv_rho, uy = m.py * inv_rho, uz = m.pz * inv_rho;
+    const float rho = 1.0f + dr;
     float d[27];
     deviation_equilibrium(d, dr, ux, uy, uz);
 
@@ -353,6 +375,13 @@ __host__ __device__ __forceinline__ CellMacro cm_collide(float (&v)[27], const R
 
     from_moments(v, ux, uy, uz);
     return CellMacro{rho, ux, uy, uz, G, phi};
+}
+
+__host__ __device__ __forceinline__ CellMacro cm_collide(float (&v)[27], const Rates& r, float Fx, float Fy,
+                                               float Fz, bool active = true, float g_given = -1.0f)
+{
+    const CellMomentum m = cm_collide_transform(v, Fx, Fy, Fz);
+    return cm_collide_relax(v, m, r, Fx, Fy, Fz, active, g_given);
 }
 
 // Shifted equilibrium populations h^eq = T m^eq(rho, u) - w (initialisation
