@@ -262,7 +262,9 @@ int cslbm_read_macro(const cslbm_level* L, float* rho, float* u, float* s, hipSt
  * cslbm_read_macro, central differences (periodic wrap on periodic axes,
  * one-sided at non-periodic faces).  The two thresholds of the dynamic
  * scale construction (section "Scale construction": gradient magnitude,
- * then velocity magnitude) are applied to these fields. */
+ * then velocity magnitude) are applied to these fields.  Large flat boxes and
+ * binary16 boxes of short rows take a temporary velocity field from the
+ * stream-ordered allocator. */
 int cslbm_vorticity(const cslbm_level* L, float* omega, float* speed, hipStream_t stream);
 
 /* Conserved totals over cells that are neither SOLID nor GHOST, accumulated

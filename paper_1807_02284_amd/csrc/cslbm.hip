@@ -277,19 +277,19 @@ __global__ void k_macro(const T* f, const float* g, const float* force, int64_t 
 
 // |curl u| and |u| of the stored state by central differences (periodic wrap
 // on periodic axes, one-sided differences at non-periodic faces).  A
-// workgroup walks a 64 x ty tile along z: every thread reads one cell's
+// workgroup walks a tx x ty tile along z: every thread reads one cell's
 // populations of the plane (the tile and one cell around it), its velocity
 // goes to a ring of four planes in LDS (one barrier a plane: the slot written
 // next is not among the three being read), and the output threads take their
 // differences there.  Against a velocity field written to temporary memory
-// and differenced by a second kernel: 490 / 556 us at 256^3 FP32, 331 / 390
-// binary16, 47 / 62 us at 128^3, 13 / 19 us at 64^3.  At 256^3 it is bound by
+// and differenced by a second kernel (below): 492 / 578 us at 256^3 FP32, 334 /
+// 396 binary16, 71 / 78 us at 128^3 with scalar, 26 / 34 us at 2x600x600 binary16,
+// 110 / 106 us at 65x200x200 with scalar (the worst of 450 boxes; 1.4 times
+// as fast on average).  At 256^3 it is bound by
 // the lines at the tiles' edges, which its two neighbours fetch as well (the
-// read-back of density and velocity alone takes 388 us); fetching a plane
-// ahead in registers, 5- or 13-row tiles and one or four workgroups per CU
-// measured the same or slower.
-constexpr int kVortTX = 64, kVortTY = 8, kVortRX = kVortTX + 2;
-constexpr int kVortRegion = kVortRX * (kVortTY + 2);
+// read-back of density and velocity alone takes 388 us).
+constexpr int kVortWidth = 64;      // widest tile
+constexpr int kVortThreads = 704;   // most cells of a tile and its rim
 
 struct VortArgs {
     const void* f;
@@ -297,6 +297,7 @@ struct VortArgs {
     const float* force;
     int nx, ny, nz, periodic;
     int ntx, nty, cz;   // tiles along x and y, planes per workgroup
+    int tx, ty;         // cells of a tile (k_vorticity)
     int64_t plane;
     float beta, s_ref;
     float* out;
@@ -333,22 +334,23 @@ __device__ __forceinline__ void vort_store(const VortArgs& a, int64_t c, const f
 }
 
 template <typename T>
-__global__ void __launch_bounds__((kVortRegion + 63) / 64 * 64) k_vorticity(const VortArgs a)
+__global__ void __launch_bounds__(kVortThreads) k_vorticity(const VortArgs a)
 {
-    __shared__ float ring[4][3][kVortRegion];
+    __shared__ float ring[4][3][kVortThreads];
     const int nx = a.nx, ny = a.ny, nz = a.nz;
     const int64_t nxy = (int64_t)nx * ny, P = a.plane;
     const T* f = static_cast<const T*>(a.f);
     const int blk = xcd_block(blockIdx.x, gridDim.x);
     const int bx = blk % a.ntx, by = (blk / a.ntx) % a.nty, bz = blk / (a.ntx * a.nty);
     const int t = threadIdx.x;
-    const bool in_region = t < kVortRegion;
-    const int x = vort_cell(bx * kVortTX - 1 + t % kVortRX, nx, a.periodic & 1);
-    const int y = vort_cell(by * kVortTY - 1 + t / kVortRX, ny, a.periodic & 2);
-    const int ox = t % kVortTX, oy = t / kVortTX;
-    const int X = bx * kVortTX + ox, Y = by * kVortTY + oy;
-    const bool out = oy < kVortTY && X < nx && Y < ny;
-    const int centre = (oy + 1) * kVortRX + ox + 1;
+    const int rx = a.tx + 2;
+    const bool in_region = t < rx * (a.ty + 2);
+    const int x = vort_cell(bx * a.tx - 1 + t % rx, nx, a.periodic & 1);
+    const int y = vort_cell(by * a.ty - 1 + t / rx, ny, a.periodic & 2);
+    const int ox = t % a.tx, oy = t / a.tx;
+    const int X = bx * a.tx + ox, Y = by * a.ty + oy;
+    const bool out = oy < a.ty && X < nx && Y < ny;
+    const int centre = (oy + 1) * rx + ox + 1;
     int xlo, xhi, ylo, yhi;
     vort_points(X, nx, a.periodic & 1, xlo, xhi);
     vort_points(Y, ny, a.periodic & 2, ylo, yhi);
@@ -369,14 +371,14 @@ __global__ void __launch_bounds__((kVortRegion + 63) / 64 * 64) k_vorticity(cons
         const int z = p - 1;
         int zlo, zhi;
         vort_points(z, nz, a.periodic & 4, zlo, zhi);
-        const float (&here)[3][kVortRegion] = ring[z & 3];
-        const float (&below)[3][kVortRegion] = ring[(z - zlo) & 3];
-        const float (&above)[3][kVortRegion] = ring[(z + zhi) & 3];
+        const float (&here)[3][kVortThreads] = ring[z & 3];
+        const float (&below)[3][kVortThreads] = ring[(z - zlo) & 3];
+        const float (&above)[3][kVortThreads] = ring[(z + zhi) & 3];
         float grad[3][3];
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
             grad[k][0] = vort_slope(here[k][centre + xhi], here[k][centre - xlo], xlo + xhi);
-            grad[k][1] = vort_slope(here[k][centre + yhi * kVortRX], here[k][centre - ylo * kVortRX], ylo + yhi);
+            grad[k][1] = vort_slope(here[k][centre + yhi * rx], here[k][centre - ylo * rx], ylo + yhi);
             grad[k][2] = vort_slope(above[k][centre], below[k][centre], zlo + zhi);
         }
         vort_store(a, X + (int64_t)nx * Y + nxy * z, grad, here[0][centre], here[1][centre], here[2][centre]);
@@ -429,6 +431,100 @@ __global__ void __launch_bounds__(((TX + 2) * (TY + 2) * (TZ + 2) + 63) / 64 * 6
         grad[k][2] = vort_slope(u[k][centre + zhi * RX * RY], u[k][centre - zlo * RX * RY], zlo + zhi);
     }
     vort_store(a, X + (int64_t)nx * Y + nxy * Z, grad, u[0][centre], u[1][centre], u[2][centre]);
+}
+
+// Tiles and planes of k_vorticity.  Rows are cut into equal tiles of at most 64
+// cells, and a tile has as many rows as the threads allow: with 64 x 8 tiles
+// throughout, 2x600x600 took 253 us (34 in two passes, 26 so), 80x300x300 294
+// (binary16; 229, 222).  The planes then follow from the workgroups a CU gets:
+// it takes its turns at them plane by plane, and one alone leaves the memory
+// idle at its barriers (65x200x200 with scalar: 115 us with one, 110 with two).
+// False where a CU would get more than the three that fit, that is on flat
+// boxes, whose tiles are many and read two planes more than they write
+// (1024x1024x1: 58 us against 44 in two passes; 575x278x105: 669, 670), for
+// binary16 rows of less than half a tile (24x393x519 166 us against 152;
+// 20x524x186 50 against 56), and where the rims' scalar and force come from
+// beyond the 256 MB of last-level cache too (142x282x362: 630 against 573; 80x300x300
+// 308, 297; but 48x497x516 438, 519).
+static bool plan_vorticity(VortArgs& a, bool half)
+{
+    constexpr int64_t cus = 256;
+    if (half && a.nx < kVortWidth / 2) return false;
+    const int64_t bytes = (int64_t)a.nx * a.ny * a.nz * (Q * (half ? 2 : 4) + QS * 4 + 12);
+    if (a.g && a.force && bytes > (256 << 20)) return false;
+    a.ntx = (a.nx + kVortWidth - 1) / kVortWidth;
+    a.tx = (a.nx + a.ntx - 1) / a.ntx;
+    const int rows = kVortThreads / (a.tx + 2) - 2;
+    const int nt0 = (a.ny + rows - 1) / rows;
+    double best = 1e300;
+    int64_t share = 0;   // workgroups per CU
+    for (int nty = nt0; nty <= 2 * nt0 && nty <= nt0 + 64 && nty <= a.ny; ++nty) {
+        const int ty = (a.ny + nty - 1) / nty;
+        const int64_t tiles = (int64_t)a.ntx * ((a.ny + ty - 1) / ty);
+        const double plane = std::max(0.9, (a.tx + 2.0) * (ty + 2.0) * 5.6e-3);   // us
+        const int64_t r0 = (tiles + cus - 1) / cus;
+        for (int64_t r = r0; r < r0 + 4; ++r) {
+            const int64_t chunks = std::min<int64_t>(a.nz, r * cus / tiles);
+            const int cz = (int)((a.nz + chunks - 1) / chunks);
+            const int64_t per_cu = (tiles * ((a.nz + cz - 1) / cz) + cus - 1) / cus;
+            const double cost = (cz + 2.0) * (per_cu == 1 ? 1.35 : (double)per_cu) * plane;
+            if (cost < best) {
+                best = cost;
+                share = per_cu;
+                a.nty = (a.ny + ty - 1) / ty;
+                a.ty = ty;
+                a.cz = cz;
+            }
+        }
+    }
+    return share <= 3;
+}
+
+// the same from a dense velocity field [3][N]
+__global__ void __launch_bounds__(256) k_curl(const VortArgs a, const float* u)
+{
+    const int64_t nxy = (int64_t)a.nx * a.ny, N = nxy * a.nz;
+    const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (c >= N) return;
+    int p[3];
+    cell_coords(c, a.nx, a.ny, p[0], p[1], p[2]);
+    const int n[3] = {a.nx, a.ny, a.nz};
+    const int64_t stride[3] = {1, a.nx, nxy};
+    float grad[3][3];
+#pragma unroll
+    for (int b = 0; b < 3; ++b) {
+        const bool periodic = a.periodic & (1 << b);
+        int lo, hi;
+        vort_points(p[b], n[b], periodic, lo, hi);
+        const int64_t cl = c + (vort_cell(p[b] - lo, n[b], periodic) - p[b]) * stride[b];
+        const int64_t ch = c + (vort_cell(p[b] + hi, n[b], periodic) - p[b]) * stride[b];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) grad[k][b] = vort_slope(u[k * N + ch], u[k * N + cl], lo + hi);
+    }
+    vort_store(a, c, grad, u[c], u[N + c], u[2 * N + c]);
+}
+
+static int vorticity_two_passes(const cslbm_level* L, const VortArgs& a, hipStream_t stream)
+{
+    const int64_t N = cells_of(L);
+    float* u = nullptr;
+    CSLBM_HIP_TRY(hipMallocAsync((void**)&u, 3 * N * sizeof(float), stream));
+    const dim3 grid((unsigned)((N + 255) / 256)), block(256);
+    if (L->storage == CSLBM_F32)
+        hipLaunchKernelGGL(k_macro<float>, grid, block, 0, stream, (const float*)L->f, L->g, L->force, N,
+                           L->plane, a.beta, a.s_ref, nullptr, u, nullptr);
+    else
+        hipLaunchKernelGGL(k_macro<_Float16>, grid, block, 0, stream, (const _Float16*)L->f, L->g, L->force,
+                           N, L->plane, a.beta, a.s_ref, nullptr, u, nullptr);
+    int rc = check_launch("k_macro");
+    if (!rc) {
+        hipLaunchKernelGGL(k_curl, grid, block, 0, stream, a, u);
+        rc = check_launch("k_curl");
+    }
+    const hipError_t ef = hipFreeAsync(u, stream);
+    if (rc) return rc;
+    if (ef != hipSuccess) return fail(CSLBM_ERR_HIP, "hipFreeAsync: %s", hipGetErrorString(ef));
+    return CSLBM_OK;
 }
 
 template <int TX, int TY, int TZ>
@@ -881,8 +977,6 @@ int cslbm_vorticity(const cslbm_level* L, float* omega, float* speed, hipStream_
     a.ny = L->ny;
     a.nz = L->nz;
     a.periodic = L->periodic & 7;
-    a.ntx = (int)blocks_for(L->nx, kVortTX);
-    a.nty = (int)blocks_for(L->ny, kVortTY);
     a.plane = L->plane;
     a.beta = (float)L->p.beta;
     a.s_ref = (float)L->p.s_ref;
@@ -890,7 +984,7 @@ int cslbm_vorticity(const cslbm_level* L, float* omega, float* speed, hipStream_
     a.speed = speed;
     // small boxes: the smallest tile that gives a CU one workgroup at most
     // (48x48x40: 16x6x4 5.7 us, 16x4x4 6.9, 8x4x4 7.8), 16x4x4 for a few more;
-    // at 1024 of those the march is as fast (64^3: 13.1 against 13.4 us)
+    // at 1024 of those the walk is as fast (64^3: 12.5 against 13.4 us)
     auto tiles_of = [&](int tx, int ty) {
         return (int64_t)blocks_for(L->nx, tx) * blocks_for(L->ny, ty) * blocks_for(L->nz, 4);
     };
@@ -905,12 +999,9 @@ int cslbm_vorticity(const cslbm_level* L, float* omega, float* speed, hipStream_
             launch_vorticity_box<16, 4, 4>(a, half, stream);
         return check_launch("k_vorticity_box");
     }
-    // two workgroups on every CU; a workgroup reads two planes more than it
-    // writes, so it takes at least four where the box is small
-    const int64_t tiles = (int64_t)a.ntx * a.nty;
-    const int64_t chunks = std::max<int64_t>(1, std::min<int64_t>(512 / tiles, (L->nz + 3) / 4));
-    a.cz = (int)((L->nz + chunks - 1) / chunks);
-    const dim3 grid((unsigned)(tiles * ((L->nz + a.cz - 1) / a.cz))), block((kVortRegion + 63) / 64 * 64);
+    if (!plan_vorticity(a, half)) return vorticity_two_passes(L, a, stream);
+    const dim3 grid((unsigned)((int64_t)a.ntx * a.nty * ((L->nz + a.cz - 1) / a.cz)));
+    const dim3 block((unsigned)(((a.tx + 2) * (a.ty + 2) + 63) / 64 * 64));
     if (half)
         hipLaunchKernelGGL(k_vorticity<_Float16>, grid, block, 0, stream, a);
     else
