@@ -392,7 +392,7 @@ def shell_tile_runs(cells: np.ndarray, shape, ratio: float, xface: bool = False)
     return c[order].astype(np.int32), offsets
 
 
-BRICK_TILE_MIN_FILL = 48   # the same, for lists from or into bricks (their gather is slower)
+BRICK_TILE_MIN_FILL = 48   # POST_TILE_MIN_FILL of post lists from or into bricks (their gather is slower)
 BRICK_PATCH_KEEP = 0.25   # a brick surface patch is kept when at least this fraction is listed
 
 
@@ -406,15 +406,32 @@ def _fitting_tile(candidates, ratio: float, buffer: int):
     return candidates[-1]
 
 
-def _group_by_tile(xyz, idx, t):
-    """Entries idx ordered by tile of t (z, y, x order; idx order inside a
-    tile), the first position of each tile and its size."""
-    k = [xyz[d][idx] // t[d] for d in range(3)]
-    key = (k[2] * (int(k[1].max()) + 1) + k[1]) * (int(k[0].max()) + 1) + k[0]
-    o = np.argsort(key, kind="stable")
-    key = key[o]
-    first = np.flatnonzero(np.r_[True, key[1:] != key[:-1]])
-    return idx[o], first, np.diff(np.r_[first, idx.size])
+# The run lists of brick-stored scales are grouped on the device (a million
+# entries: 1 ms against 16 ms of numpy sorting; every region rebuild makes
+# them anew).
+def _group_by_tile(c, shape, t):
+    """Box cells c (a tensor) by tile of t in (z, y, x) order of the tiles, c's
+    order inside a tile: the permutation, and each tile's number of cells."""
+    nx, ny = shape[0], shape[1]
+    row = c // nx
+    k = ((row // ny // t[2]) * ((ny - 1) // t[1] + 1) + row % ny // t[1]) * ((nx - 1) // t[0] + 1) + c % nx // t[0]
+    k, order = torch.sort(k, stable=True)
+    return order, torch.unique_consecutive(k, return_counts=True)[1]
+
+
+def _offsets(sizes):
+    """int32 run offsets, 0 first, of runs of these sizes."""
+    end = torch.cumsum(sizes, 0).to(torch.int32)
+    return torch.cat([end.new_zeros(1), end])
+
+
+def _split_runs(size):
+    """Sizes of the runs of at most POST_RUN entries that tiles of these sizes
+    are cut into."""
+    pieces = (size + POST_RUN - 1) // POST_RUN
+    first = torch.cumsum(pieces, 0) - pieces
+    k = torch.arange(int(pieces.sum()), device=size.device) - torch.repeat_interleave(first, pieces)
+    return torch.clamp(torch.repeat_interleave(size, pieces) - k * POST_RUN, max=POST_RUN)
 
 
 def brick_post_runs(cells: np.ndarray, shape, ratio: float, dst_bricks: bool):
@@ -427,9 +444,16 @@ def brick_post_runs(cells: np.ndarray, shape, ratio: float, dst_bricks: bool):
     whose 32-byte stores are a quarter of a line; from bricks into bricks
     (600 000 targets, ratio 4/3) 215 us gathered, 99 in tiles.  Returns
     (cells in run order, offsets)."""
+    c, offsets = _brick_post_runs(torch.as_tensor(np.asarray(cells, np.int32)), shape, ratio, dst_bricks)
+    return c.numpy(), offsets.numpy()
+
+
+def _brick_post_runs(c, shape, ratio: float, dst_bricks: bool):
+    """brick_post_runs of an ascending int32 tensor, in tensors."""
     tiles = ((8, 8, 4), (8, 8, 2), (8, 4, 2), (4, 4, 2), (4, 2, 1)) if dst_bricks else \
         ((32, 4, 2), (16, 4, 4), (16, 4, 2), (8, 4, 2), (4, 4, 2), (4, 2, 1))
-    return post_tile_runs(cells, shape, ratio, tile=_fitting_tile(tiles, ratio, POST_TILE_BUFFER))
+    order, size = _group_by_tile(c, shape, _fitting_tile(tiles, ratio, POST_TILE_BUFFER))
+    return c[order], _offsets(size)
 
 
 def brick_ghost_runs(cells: np.ndarray, shape, ratio: float):
@@ -442,34 +466,33 @@ def brick_ghost_runs(cells: np.ndarray, shape, ratio: float):
     of one brick's ghosts throughout took 3 % more of the whole step.  ``ratio`` is the
     scale's spacing over its parent's.  Returns (cells in run order, offsets
     with one entry more than there are runs)."""
-    c = np.sort(np.asarray(cells, np.int64))
-    nx, ny = shape[0], shape[1]
-    xyz = (c % nx, (c // nx) % ny, c // (nx * ny))
-    left = np.arange(c.size)
-    parts, offsets = [], [0]
+    c, offsets = _brick_ghost_runs(torch.as_tensor(np.asarray(cells, np.int32)), shape, ratio)
+    return c.numpy(), offsets.numpy()
+
+
+def _brick_ghost_runs(cells, shape, ratio: float):
+    """brick_ghost_runs of an int32 tensor, in tensors."""
+    left = torch.sort(cells)[0]
+    parts, sizes = [], []
     for candidates in (((32, 8, 1), (16, 8, 1), (8, 8, 1)), ((32, 1, 8), (16, 1, 8), (8, 1, 8)),
                        ((1, 16, 16), (1, 8, 16), (1, 8, 8))):
-        if left.size == 0:
+        if left.numel() == 0:
             break
         t = _fitting_tile(candidates, ratio, SHELL_TILE_BUFFER)
-        idx, first, size = _group_by_tile(xyz, left, t)
+        order, size = _group_by_tile(left, shape, t)
         keep = size >= BRICK_PATCH_KEEP * math.prod(t)
-        listed = np.repeat(keep, size)
-        parts.append(idx[listed])
-        offsets.extend((offsets[-1] + np.cumsum(size[keep])).tolist())
-        left = np.sort(idx[~listed])
-    if left.size:
+        listed = torch.repeat_interleave(keep, size)
+        parts.append(left[order[listed]])
+        sizes.append(size[keep])
+        left = torch.sort(left[order[~listed]])[0]
+    if left.numel():
         t = _fitting_tile(((8, 8, 8), (8, 8, 4), (8, 4, 4), (4, 4, 4)), ratio, SHELL_TILE_BUFFER)
-        idx, first, size = _group_by_tile(xyz, left, t)
-        parts.append(idx)
-        base = offsets[-1]
-        for a, n in zip(first.tolist(), size.tolist()):
-            offsets.extend(range(base + a + POST_RUN, base + a + n, POST_RUN))
-            offsets.append(base + a + n)
-    offsets = np.asarray(offsets, np.int32)
-    assert np.all(np.diff(offsets) <= POST_RUN)
-    order = np.concatenate(parts) if parts else left
-    return c[order].astype(np.int32), offsets
+        order, size = _group_by_tile(left, shape, t)
+        parts.append(left[order])
+        sizes.append(_split_runs(size))
+    if not parts:
+        return left, _offsets(left.to(torch.int64))
+    return torch.cat(parts), _offsets(torch.cat(sizes))
 
 
 def _nodes_coincide(src: Level, dst: Level) -> bool:
@@ -483,15 +506,28 @@ def _nodes_coincide(src: Level, dst: Level) -> bool:
                ((dst.c.origin[d] - src.c.origin[d]) / src.c.dx for d in range(3)))
 
 
-def _storage_list(lev: Level, box_cells: np.ndarray) -> np.ndarray:
-    """A cell list over a level's box in the level's storage order (int32);
-    every listed cell of a brick level must be stored."""
+def _int32_list(cells, device) -> torch.Tensor:
+    """A cell list (array or tensor) as a contiguous int32 tensor on device."""
+    if not torch.is_tensor(cells):
+        cells = torch.as_tensor(np.ascontiguousarray(cells, np.int32))
+    return cells.to(device, torch.int32).contiguous()
+
+
+def _storage_list(lev: Level, box_cells) -> torch.Tensor:
+    """A cell list over a level's box (array or tensor) in the level's storage
+    order, int32 on its device; every listed cell of a brick level must be
+    stored."""
+    c = _int32_list(box_cells, lev.device)
     if lev.dense_index is None:   # a dense box: storage order is box order
-        return np.asarray(box_cells, np.int32)
-    idx = lev.storage_of(np.asarray(box_cells, np.int64))
-    if np.any(idx < 0):
+        return c
+    if c.numel() == 0:
+        return c
+    if int(c.min()) < 0 or int(c.max()) >= lev.n_box:
+        raise ValueError("box cell index outside the level's box")
+    idx = lev.storage_on_device(c)
+    if int(idx.min()) < 0:
         raise ValueError("a listed cell lies in a brick that is not stored")
-    return idx.astype(np.int32)
+    return idx
 
 
 class Hierarchy:
@@ -597,15 +633,15 @@ class Hierarchy:
                         and not _nodes_coincide(par, lev)):
                     # a brick-stored scale or parent: patches of the stored
                     # region's staircase surface
-                    ghosts, runs = brick_ghost_runs(ghosts, (lev.nx, lev.ny), lev.c.dx / par.c.dx)
-                    r_t = torch.as_tensor(runs, device=dev)
+                    ghosts, r_t = _brick_ghost_runs(torch.as_tensor(ghosts, device=dev),
+                                                    (lev.nx, lev.ny), lev.c.dx / par.c.dx)
                     self.lists.append(r_t)
-                    sc.n_ghost_tiles = runs.size - 1
+                    sc.n_ghost_tiles = r_t.numel() - 1
                     sc.ghost_tiles = r_t.data_ptr()
-                g_t = torch.as_tensor(_storage_list(lev, ghosts), device=dev)
+                g_t = _storage_list(lev, ghosts)
                 self.lists.append(g_t)
-                sc.n_ghost = ghosts.size
-                sc.ghost_cells = g_t.data_ptr() if ghosts.size else None
+                sc.n_ghost = g_t.numel()
+                sc.ghost_cells = g_t.data_ptr() if g_t.numel() else None
                 if self.far[i]:
                     # reversed rules: post-map onto the parent's boundary shell
                     pk = self.kinds[self.parents[i]]
@@ -640,7 +676,8 @@ class Hierarchy:
                 shape = (levels[j].nx, levels[j].ny)
                 min_fill = tile_min_fill
                 if bricks:
-                    tiled, runs = brick_post_runs(cells, shape, ratio, levels[j].dense_index is not None)
+                    tiled, runs = _brick_post_runs(torch.as_tensor(cells, device=dev), shape, ratio,
+                                                   levels[j].dense_index is not None)
                     min_fill = min(min_fill, BRICK_TILE_MIN_FILL)
                 else:
                     tiled, runs = post_tile_runs(cells, shape, ratio)
@@ -649,17 +686,20 @@ class Hierarchy:
                         # too sparse for plane tiles: a list in thin plates
                         # fills tiles lying in those plates
                         tiled, runs = plate_tile_runs(cells, shape, ratio)
-                if tiled.size >= min_fill * (runs.size - 1):
+                if len(tiled) >= min_fill * (len(runs) - 1):
                     cells = tiled
-                    self.post[(i, j)] = cells
+                    if not bricks:
+                        self.post[(i, j)] = cells
                     r_t = torch.as_tensor(runs, device=dev)
                     self.lists.append(r_t)
-                    self.c_scales[i].n_post_tiles[j] = runs.size - 1
+                    self.c_scales[i].n_post_tiles[j] = len(runs) - 1
                     self.c_scales[i].post_tiles[j] = r_t.data_ptr()
-            t = torch.as_tensor(_storage_list(levels[j], cells), device=dev)
+            t = _storage_list(levels[j], cells)
             self.lists.append(t)
-            self.c_scales[i].n_post[j] = cells.size
-            self.c_scales[i].post_cells[j] = t.data_ptr() if cells.size else None
+            self.c_scales[i].n_post[j] = t.numel()
+            self.c_scales[i].post_cells[j] = t.data_ptr() if t.numel() else None
+        if dev.type == "cuda":   # a first step on another stream finds the lists there
+            torch.cuda.current_stream(dev).synchronize()
         self.c = _capi.CslbmHierarchy(n, 0, C.cast(self.c_scales, C.POINTER(_capi.CslbmScale)))
 
     def ghost_cells(self, i: int) -> np.ndarray:
@@ -922,9 +962,9 @@ def kept_cells(old: Level, old_kinds: np.ndarray, new: Level, new_kinds: np.ndar
     return (c_old[keep].to(torch.int32).cpu().numpy(), c_new[keep].to(torch.int32).cpu().numpy())
 
 
-def copy_cells(src: Level, src_cells: np.ndarray, dst: Level, dst_cells: np.ndarray, stream=None):
-    a = torch.as_tensor(np.asarray(src_cells, np.int32), device=dst.device)
-    b = torch.as_tensor(np.asarray(dst_cells, np.int32), device=dst.device)
+def copy_cells(src: Level, src_cells, dst: Level, dst_cells, stream=None):
+    a = _int32_list(src_cells, dst.device)
+    b = _int32_list(dst_cells, dst.device)
     src._sync_struct()
     dst._sync_struct()
     _capi.call("cslbm_copy_cells", C.byref(src.c), a.data_ptr(), C.byref(dst.c), b.data_ptr(),

@@ -182,12 +182,19 @@ class Level:
         table = getattr(self, "brick_table", None)
         if table is not None and table.is_cuda:
             d = torch.as_tensor(dense, device=table.device)
-            x, y, z = d % nx, (d // nx) % ny, d // (nx * ny)
-            b = table[(x >> 3) + bnx * ((y >> 3) + bny * (z >> 3))].to(torch.int64)
-            return torch.where(b < 0, -1, b * 512 + (x & 7) + 8 * (y & 7) + 64 * (z & 7)).cpu().numpy()
+            return Level.storage_on_device(self, d).cpu().numpy()
         x, y, z = dense % nx, (dense // nx) % ny, dense // (nx * ny)
         b = self._table[(x >> 3) + bnx * ((y >> 3) + bny * (z >> 3))].astype(np.int64)
         return np.where(b < 0, -1, b * 512 + (x & 7) + 8 * (y & 7) + 64 * (z & 7))
+
+    def storage_on_device(self, dense: torch.Tensor) -> torch.Tensor:
+        """storage_of for a tensor of box cells on a brick level's device (the
+        cells inside the box)."""
+        nx, ny, bnx, bny = self.nx, self.ny, self.nx // 8, self.ny // 8
+        row = dense // nx
+        x, y, z = dense % nx, row % ny, row // ny
+        b = self.brick_table[(x >> 3) + bnx * ((y >> 3) + bny * (z >> 3))].to(dense.dtype)
+        return torch.where(b < 0, -1, b * 512 + (x & 7) + 8 * (y & 7) + 64 * (z & 7))
 
     def to_storage(self, box_values: np.ndarray) -> np.ndarray:
         """Per-cell values over the box ([..., n_box]) in storage order."""
