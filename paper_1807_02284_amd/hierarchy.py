@@ -542,7 +542,8 @@ class Hierarchy:
 
     A post-mapping list from a finer scale into a coarser one is
     grouped into tiles (``tile_posts``) when they hold ``tile_min_fill``
-    targets on average: plane tiles (post_tile_runs), or, where those are too
+    targets on average (three eighths of that with a brick-stored scale on
+    either side, whose gather is slower): plane tiles (post_tile_runs), or, where those are too
     sparse (``tile_plates`` "sparse"; "always": for every such list;
     "never"), tiles lying in the list's thin plates (plate_tile_runs); with a
     brick-stored scale on either side brick_post_runs.  The
@@ -678,7 +679,7 @@ class Hierarchy:
                 if bricks:
                     tiled, runs = _brick_post_runs(torch.as_tensor(cells, device=dev), shape, ratio,
                                                    levels[j].dense_index is not None)
-                    min_fill = min(min_fill, BRICK_TILE_MIN_FILL)
+                    min_fill = tile_min_fill * BRICK_TILE_MIN_FILL / POST_TILE_MIN_FILL
                 else:
                     tiled, runs = post_tile_runs(cells, shape, ratio)
                     if tile_plates == "always" or (tile_plates == "sparse" and
