@@ -538,35 +538,40 @@ static bool marches(const cslbm_level* L)
 }
 
 // The tile of k_step_pair_box for a level, -1 where two single steps are
-// faster or as fast.  Both sides are estimated in us from lines through the
-// measured times of 160 random boxes of 2k-600k cells: a pair costs a launch
-// and, on the CU that has most tiles, their first- and second-step waves; a
-// step a launch, its 256-thread blocks (more where rows are shorter than a few
-// 32-byte sectors) and the cells that outgrow the L2s.  Which side wins
-// changes with how the tiles fill the last round over 256 CUs (with scalar
-// and force 66x62x19: 8.1 us per step against 7.8 single; 45x23x77: 7.0
-// against 8.2), so a limit on the cells alone would not do.
+// faster or as fast.  Both sides are estimated in us from fits to the times of
+// 900 random boxes of 1k-520k cells (they leave 6-9 %): a pair costs a launch
+// and its tiles' first- and second-step waves, counted on average and on the
+// CU that has most; a step a launch, its 256-thread blocks, its cells, and
+// those that outgrow the L2s.  Which side wins changes with how the tiles fill
+// the last round over 256 CUs (with scalar and force 66x62x19: 8.1 us per step
+// against 7.8 single; 45x23x77: 7.0 against 8.2), so a limit on the cells alone
+// would not do.  A pair has to be ahead by 11 %: 4 of the 525 boxes that pair
+// lose more than 2 % (10 % at worst), 17 of 622 would at 5 %.
 static int box_tile(const cslbm_level* L)
 {
     constexpr int tx[3] = {8, 8, 16}, ty[3] = {4, 6, 4}, tz = 4;
-    constexpr double wave_us[2][3] = {{0.33, 0.285, 0.265}, {0.44, 0.36, 0.0}};
+    // launch, wave of the CU with most tiles, wave on average
+    constexpr double pair_us[2][3][3] = {{{5.2, 0.22, 0.14}, {5.15, 0.21, 0.12}, {5.2, 0.167, 0.14}},
+                                         {{5.0, 0.33, 0.14}, {5.4, 0.24, 0.177}, {}}};
     const int64_t cells = cells_of(L);
     const bool scalar = L->g != nullptr;
     if (cells > kBoxCells) return -1;
     const dim3 b = step_block(L->nx);
     const double rounds = (double)((L->nx + b.x - 1) / b.x) * ((L->ny + b.y - 1) / b.y) * L->nz / 256.0;
-    const double spill = std::max((double)cells - (scalar ? 0.9e5 : 1.4e5), 0.0);
-    const double work = scalar ? 1.45 * rounds + 6e-5 * spill : 1.65 * rounds + 4e-5 * spill;
-    const double single = (scalar ? 3.5 : 3.8) + (L->nx < 24 ? 1.25 : 1.0) * work;
+    const double spill = std::max((double)cells - 1.2e5, 0.0);
+    const double single = scalar ? 4.25 + 0.85 * rounds + 2.25e-5 * (double)cells + 2.45e-5 * spill
+                                 : 4.2 + 0.66 * rounds + 1.95e-5 * (double)cells + 1.5e-5 * spill;
     int tile = -1;
-    double best = 0.92 * 2.0 * std::max(single, 4.6);
+    double best = 0.89 * 2.0 * single;
     for (int k = 0; k < (scalar ? 2 : 3); ++k) {
         // one period brings a halo cell inside
         if (L->nx < tx[k] || L->ny < ty[k] || L->nz < tz) continue;
         const int64_t blocks = (int64_t)((L->nx + tx[k] - 1) / tx[k]) * ((L->ny + ty[k] - 1) / ty[k]) *
                                ((L->nz + tz - 1) / tz);
         const int waves = ((tx[k] + 2) * (ty[k] + 2) * (tz + 2) + 63) / 64 + (tx[k] * ty[k] * tz + 63) / 64;
-        const double us = (scalar ? 5.2 : 4.8) + wave_us[scalar][k] * (double)((blocks + 255) / 256 * waves);
+        const double(&c)[3] = pair_us[scalar][k];
+        const double most = c[1] + (L->force ? 0.03 : 0.0);
+        const double us = c[0] + waves * (most * (double)((blocks + 255) / 256) + c[2] * (double)blocks / 256.0);
         if (us < best) {
             best = us;
             tile = k;
