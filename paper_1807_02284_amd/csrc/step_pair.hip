@@ -22,9 +22,9 @@
 // were slower (530-580 us).
 //
 // What bounds it: VALU issue, busy 81 % of the time at 256^3; HBM moves
-// 4.5 TB/s.  Per step, pair against k_step: 424 / 642 us at 256^3, 58 / 82 us
-// at 128^3, 61 / 105 us at 181x118x77 (rows off the cache lines), 28 / 39 us
-// at 96^3; with force and scalar 77 / 108 us at 128^3.  binary16 levels stay
+// 4.5 TB/s.  Per step, pair against k_step: 418 / 645 us at 256^3, 55 / 83 us
+// at 128^3, 60 / 104 us at 181x118x77 (rows off the cache lines), 28 / 38 us
+// at 96^3; with force and scalar 76 / 108 us at 128^3.  binary16 levels stay
 // with k_step: it already issues VALU instructions 87 % of the time.
 #include <hip/hip_runtime.h>
 
@@ -315,9 +315,10 @@ __global__ void __launch_bounds__((PairShape<TX, TY>::kThreads))
 // Rows per tile and planes per workgroup.  One workgroup runs on a CU at a
 // time; the workgroups run in rounds of 256, each computes two planes more
 // than it outputs, and a plane takes its first- and second-step waves per SIMD
-// and half a wave for the barrier.  Measured at 256^3 (one LDS plane): 64 x 8
-// tiles of 128 planes (256 workgroups) 486 us per step, 64 x 13 of 86 planes
-// (240) 500, 64 x 11 of 32 planes (768) 513.
+// and half a wave for the barrier.  Measured at 256^3: 64 x 8 tiles of 128
+// planes (256 workgroups) 419 us per step, of 64 planes 456, of 32 planes 463;
+// 64 x 9 of 128 planes (232) 512; tiles of 13 rows and one LDS plane 472 (64 us
+// against 57 at 128^3, 61 against 61 at 181x118x77).
 template <int TX, int TY>
 static void plan_tiles(PairArgs& a)
 {
@@ -359,11 +360,11 @@ static void launch_pair(PairArgs a, hipStream_t st)
 // The same pair for levels too small to march: one TX x TY x TZ tile per
 // workgroup, the first step on it and one cell around it (a thread per cell)
 // into LDS, one barrier, the second step from there.  What bounds a small
-// step is its launch and the round trip to memory (4.3-4.6 us at 16^3 and at
+// step is its launch and the round trip to memory (4.3-4.7 us at 16^3 and at
 // 32^3 alike); two and a half times the first step's arithmetic costs less
-// than a second trip.  Per step, pair against k_step: 3.6 / 4.6 us at 32^3,
-// 6.1 / 8.3 us at 48^3, 10.5 / 12.2 us at 64^3, 15.1 / 21.4 us at 72^3; with
-// scalar and force 4.2 / 4.8 us at 32^3, 20.5 / 26.9 us at 72^3.  Larger tiles
+// than a second trip.  Per step, pair against k_step: 3.8 / 4.7 us at 32^3,
+// 6.6 / 8.4 us at 48^3, 10.9 / 12.2 us at 64^3, 16.5 / 21.9 us at 72^3; with
+// scalar and force 4.3 / 4.9 us at 32^3, 21.3 / 27.4 us at 72^3.  Larger tiles
 // share more but leave SIMDs idle or hold one workgroup per CU: 8x8x8 at 32^3
 // 4.9 us, 8x8x4 4.1, 16x6x4 4.6; 4x4x4 at 64^3 17.5.
 template <int TX, int TY, int TZ>
@@ -508,9 +509,9 @@ static PairArgs pair_args(const cslbm_level* L, const void* fin, void* fout, con
 }
 
 // Tiles 64 cells wide, or 32 where the rows are multiples of half a cache
-// line and 64 would leave more lanes past the row's end (96^3: 27.5 against
-// 35 us per step).  With other row lengths a 32-wide tile writes every line in
-// parts (181x118x77: 70 against 54 us, one LDS plane).
+// line and 64 would leave more lanes past the row's end (96^3: 28 against 31
+// us per step, 80x300x100 with scalar 109, 117).  With other row lengths a
+// 32-wide tile writes every line in parts (181x118x77: 72 against 60 us).
 static bool narrow_tiles(const cslbm_level* L)
 {
     const int w32 = (L->nx + 31) / 32 * 32, w64 = (L->nx + 63) / 64 * 64;
@@ -519,21 +520,20 @@ static bool narrow_tiles(const cslbm_level* L)
 
 // Whether a pair marches along z: enough cells to give every CU a tile of
 // some planes (cells times the used part of the tiles' width; per step at
-// 64^3 12.8 us against 12.1 single, 64x64x128 16.8 against 21.6) and a few
-// rows and planes for the halo to stay small (288x288x8: 25 against 30;
-// 256x8x150: 15.1 against 15.7).  Lane offsets in a plane are 32-bit bytes.
-// Up to 2^19 cells, where the small tiles were measured, those take rows that
-// leave much of the marching tiles empty (75x145x43: 22.4 us against 26.8;
-// 40x100x120: 19.9 against 23.9; 137x100x37: 23.8 against 25.5; but 95x64x80,
-// 74 % used, with scalar: 27.8 against 25.7).
+// 64^3 12.3 us against 12.0 single, 64x64x128 17 against 22) and a few rows
+// and planes for the halo to stay small (288x288x8: 26 against 31).  Lane offsets in a plane are 32-bit bytes.
+// Up to 2^19 cells the small tiles are the better way for fewer than 30 rows
+// or planes (with force 96x28x141 19.7 us marching, 16.5 on tiles, 18.1 single;
+// 64x23x191 14.8, 13.7, 14.2).
 constexpr int64_t kBoxCells = 1 << 19;
 
 static bool marches(const cslbm_level* L)
 {
-    if (L->ny < 8 || L->nz < 8 || (int64_t)L->nx * L->ny >= (1 << 30)) return false;
+    const int least = std::min(L->ny, L->nz);
+    if (least < 8 || (int64_t)L->nx * L->ny >= (1 << 30)) return false;
+    if (cells_of(L) <= kBoxCells && least < 30) return false;
     const int tx = narrow_tiles(L) ? 32 : 64;
     const double used = (double)L->nx / ((L->nx + tx - 1) / tx * tx);
-    if (cells_of(L) <= kBoxCells && used < (L->nx > 64 ? 0.72 : 0.65)) return false;
     return (double)cells_of(L) * used > (double)(1 << 18);
 }
 
@@ -607,7 +607,7 @@ int launch_step_pair(const cslbm_level* L, const void* fin, void* fout, const fl
         return check_launch("k_step_pair_box");
     }
     const bool narrow = narrow_tiles(L);
-    // twelve waves, three per SIMD (the scalar takes 154-167 VGPRs)
+    // at most twelve waves, three per SIMD (the scalar takes 154-167 VGPRs)
     if (gin && L->force) {
         if (narrow)
             launch_pair<true, true, 32, 16, 3>(a, stream);
