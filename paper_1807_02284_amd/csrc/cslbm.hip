@@ -930,7 +930,7 @@ int cslbm_step(cslbm_level* L, int32_t n_steps, hipStream_t stream)
     // fused pairs: an even number of them, so that the buffers' roles after
     // n_steps are those of n_steps single steps, and at least one single step
     // after them, so that f_next holds the state before the last step
-    if (n_steps >= 5 && step_pair_applies(L))
+    if (n_steps >= 5 && step_pair_kind(L) != PairKind::kNone)
         for (const int paired = (n_steps - 1) / 4 * 4; n < paired; n += 2) {
             rc = launch_step_pair(L, L->f, L->f_next, L->g, L->g_next, stream);
             if (rc) return rc;

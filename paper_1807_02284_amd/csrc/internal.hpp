@@ -53,8 +53,10 @@ int launch_step_into(const cslbm_level* L, const void* fin, void* fout, const fl
                      float* gout, hipStream_t stream);
 
 // Two such steps in one launch, the state between them kept on the chip
-// (step_pair.hip), for levels step_pair_applies accepts.
-bool step_pair_applies(const cslbm_level* L);
+// (step_pair.hip), for levels that step_pair_kind gives a kernel:
+// k_step_pair_box or k_step_pair.
+enum class PairKind : int { kNone = 0, kTiles = 1, kMarch = 2 };
+PairKind step_pair_kind(const cslbm_level* L);
 int launch_step_pair(const cslbm_level* L, const void* fin, void* fout, const float* gin, float* gout,
                      hipStream_t stream);
 

@@ -521,7 +521,8 @@ static bool narrow_tiles(const cslbm_level* L)
 // Whether a pair marches along z: enough cells to give every CU a tile of
 // some planes (cells times the used part of the tiles' width; per step at
 // 64^3 12.3 us against 12.0 single, 64x64x128 17 against 22) and a few rows
-// and planes for the halo to stay small (288x288x8: 26 against 31).  Lane offsets in a plane are 32-bit bytes.
+// and planes for the halo to stay small (288x288x8: 26 against 31).  Lane
+// offsets in a plane are 32-bit bytes.
 // Up to 2^19 cells the small tiles are the better way for fewer than 30 rows
 // or planes (with force 96x28x141 19.7 us marching, 16.5 on tiles, 18.1 single;
 // 64x23x191 14.8, 13.7, 14.2).
@@ -582,12 +583,13 @@ static int box_tile(const cslbm_level* L)
 
 // Levels whose pairs of steps run faster fused: fully periodic FP32 boxes
 // without flags or gradient mode.
-bool step_pair_applies(const cslbm_level* L)
+PairKind step_pair_kind(const cslbm_level* L)
 {
     if (L->storage != CSLBM_F32 || L->flags || L->brick_table || (L->periodic & 7) != 7 ||
         L->p.grad_mode != 0)
-        return false;
-    return marches(L) || box_tile(L) >= 0;
+        return PairKind::kNone;
+    if (marches(L)) return PairKind::kMarch;
+    return box_tile(L) >= 0 ? PairKind::kTiles : PairKind::kNone;
 }
 
 int launch_step_pair(const cslbm_level* L, const void* fin, void* fout, const float* gin, float* gout,

@@ -8,14 +8,12 @@ import dataclasses
 import pytest
 import torch
 
+from test_pair_kernels import MARCHING, TILED, WIDE_TILED
 from test_parity_pair import level
 
 pytestmark = pytest.mark.gpu
 
-# marching, 64-wide: full tiles, a last tile of one column, eight planes; 32-wide:
-# whole and partial tiles.  Small tiles: one, whole ones, last tiles of one cell.
-SHAPES = [(64, 64, 66), (193, 67, 45), (256, 264, 8), (96, 70, 45), (80, 61, 66),
-          (32, 32, 32), (33, 29, 35), (15, 121, 41), (8, 4, 4)]
+SHAPES = MARCHING + TILED + WIDE_TILED
 OPTIONS = [(False, False), (True, True), (True, False), (False, True)]
 
 
