@@ -42,11 +42,17 @@ class Params:
             self.beta, self.s_ref, (C.c_double * 3)(*self.u_in), self.s_in)
 
 
+# the current stream's handle without a Stream object, whose making takes 2.9 us
+# of a 9 us step call (not a documented name: the object where torch lacks it)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream_handle(stream=None) -> int:
     if stream is None:
-        # the current stream of the current device as torch keeps it; making
-        # the Stream object first takes 2.9 us of a 9 us step call
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        device = torch.cuda.current_device()   # raises without a GPU and in a forked child
+        if _raw_stream is not None:
+            return _raw_stream(device)
+        stream = torch.cuda.current_stream(device)
     return int(stream.cuda_stream)
 
 
