@@ -190,8 +190,9 @@ inline ExchArgs exchange_args(const cslbm_level* src, const void* fA, const void
 
 // One exchange launch (validated arguments); defined with the kernels.
 // With runs (n_runs + 1 offsets grouping the list into runs of at most 256
-// entries), an exchange from a dense source into a dense destination that
-// the tiled kernel handles maps one run per workgroup through LDS.
+// entries), an exchange that the tiled kernel handles (one time level, no
+// periodic source axis, targets off the source lattice points; boxes or
+// bricks on either side) maps one run per workgroup through LDS.
 int launch_exchange(const cslbm_level* src, const void* fA, const void* fB, const float* gA,
                     const float* gB, double w, const cslbm_level* dst, void* f_out, float* g_out,
                     const int32_t* cells, int32_t n_cells, hipStream_t stream,

@@ -201,8 +201,8 @@ __global__ void __launch_bounds__(256) k_exchange(const ExchArgs a)
 // Lanes past the run's end repeat its first entry: they compute the same
 // bits as lane 0 and store them to the same cell.  kShell: runs that are
 // patches of a ghost shell (small source boxes), blended or not; otherwise
-// post-mapping runs (one time level).
-template <typename Ts, typename Td, bool kScalar, bool kShell, bool kBlend>
+// post-mapping runs (one time level), of a source in bricks with kBricks.
+template <typename Ts, typename Td, bool kScalar, bool kShell, bool kBlend, bool kBricks = false>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
 k_exchange_tiled(const ExchArgs a, const int32_t* runs)
 {
@@ -214,7 +214,8 @@ k_exchange_tiled(const ExchArgs a, const int32_t* runs)
             return;
     } else {
         __shared__ TileLds lds;
-        if (!tile_interp<Ts, kScalar>(a, runs, lds, T, v, gi)) return;
+        if (!tile_interp<Ts, kScalar, false, kTileLoads, kTilePlanes, false, kBricks>(a, runs, lds, T, v, gi))
+            return;
     }
     map_and_store<Td>(a, T.c, v, gi, kScalar);
 }
@@ -368,7 +369,12 @@ static void launch_tiled_kernel(const ExchArgs& a, const int32_t* runs, int32_t 
                                 bool blend, hipStream_t st)
 {
     const dim3 grid((unsigned)n_runs), block(256);
-    if (!shell) {
+    if (!shell && a.sb.table) {
+        if (a.gA)
+            hipLaunchKernelGGL((k_exchange_tiled<Ts, Td, true, false, false, true>), grid, block, 0, st, a, runs);
+        else
+            hipLaunchKernelGGL((k_exchange_tiled<Ts, Td, false, false, false, true>), grid, block, 0, st, a, runs);
+    } else if (!shell) {
         if (a.gA)
             hipLaunchKernelGGL((k_exchange_tiled<Ts, Td, true, false, false>), grid, block, 0, st, a, runs);
         else

@@ -4,9 +4,9 @@
 //
 // No periodic source axis, targets off the source lattice points; either side
 // may be stored in bricks (a box cell whose brick is not stored is never a
-// corner of weight and loads storage cell 0).  One workgroup takes one run of the target list
-// (the host groups neighbouring cells of the destination into runs of at
-// most 256: a tile of a few rows).  The source cells the run's stencils
+// corner of weight and loads storage cell 0).  One workgroup takes one run of
+// the target list (the host groups neighbouring cells of the destination into
+// runs of at most 256: a tile of a few rows).  The source cells the run's stencils
 // reach form a small box (a 32 x 8 x 1 tile at spacing ratio 4/3 reaches at
 // most 44 x 12 x 2 of them); the workgroup copies that box into LDS a few
 // population planes at a time with row-wise coalesced loads, and each
@@ -89,8 +89,14 @@ struct TileTarget {
 // x-face copies of a ghost shell's prior-mapping) reads that copy, with the
 // corner indices shifted as in the direct gather, and a target whose
 // stencil leaves the copy becomes NaN as there; runs must not mix segments.
+// kBricks: the source of a post list is stored in bricks.  A compile-time
+// switch: with the table tested at run time a dense source's launch of few
+// runs was slower (1387 runs of a 512x256x256 plume: 144 us against 133).
+// Shell runs (kStaged) test it at run time: that code takes 95 registers
+// instead of 100 (five waves per SIMD, not four) and is the faster one for
+// dense sources too (82.2 -> 80.9 us and 136 -> 132 us a launch there).
 template <typename Ts, bool kScalar, bool kBlend = false, int kLoads = kTileLoads,
-          int kPlanes = kTilePlanes, bool kStaged = false>
+          int kPlanes = kTilePlanes, bool kStaged = false, bool kBricks = false>
 __device__ __forceinline__ bool tile_interp(const ExchArgs& a, const int32_t* runs,
                                             TileBuf<kLoads, kPlanes>& L, TileTarget& T,
                                             float (&v)[27], float (&gi)[QS])
@@ -181,14 +187,15 @@ __device__ __forceinline__ bool tile_interp(const ExchArgs& a, const int32_t* ru
     for (int q = 0; q < 27; ++q) v[q] = 0.0f;
 #pragma unroll
     for (int i = 0; i < QS; ++i) gi[i] = 0.0f;
+    const bool sbrick = kStaged ? a.sb.table != nullptr : kBricks;
     if (V > kCap) {   // uniform: direct gather
 #pragma unroll 1   // one corner at a time: this rare path must not raise the register count
         for (int corner = 0; corner < 8; ++corner) {
             const float wt = corner_weight(T.t, corner);
             const int cx = corner & 1 ? T.hi[0] : T.lo[0], cy = corner & 2 ? T.hi[1] : T.lo[1];
             const int cz = corner & 4 ? T.hi[2] : T.lo[2];
-            const int64_t sc = a.sb.table ? source_cell(a, cx, cy, cz)
-                                          : cx + (int64_t)n[0] * (cy + (int64_t)n[1] * cz);
+            const int64_t sc = sbrick ? source_cell(a, cx, cy, cz)
+                                      : cx + (int64_t)n[0] * (cy + (int64_t)n[1] * cz);
 #pragma unroll
             for (int i = 0; i < Q; ++i) {
                 const float hA = Io<Ts>::ld(fA + i * P + sc);
@@ -212,14 +219,14 @@ __device__ __forceinline__ bool tile_interp(const ExchArgs& a, const int32_t* ru
         return true;
     }
     // source offsets of this thread's box elements (the same in every plane)
-    const bool sbrick = a.sb.table != nullptr;
     const int64_t origin = sbrick ? 0 : x0 + (int64_t)n[0] * (y0 + (int64_t)n[1] * z0);
     int eoff[kLoads];
 #pragma unroll
     for (int k = 0; k < kLoads; ++k) {
         const int e = min(tid + 256 * k, V - 1);
         const int ex = e % bx, ey = (e / bx) % by, ez = e / (bx * by);
-        eoff[k] = sbrick ? (int)source_cell(a, x0 + ex, y0 + ey, z0 + ez) : ex + n[0] * (ey + n[1] * ez);
+        eoff[k] = sbrick ? (int)source_cell(a, x0 + ex, y0 + ey, z0 + ez)
+                         : ex + n[0] * (ey + n[1] * ez);
     }
     int cl[8];
     float wt[8];
