@@ -21,8 +21,8 @@
 // they need 27 more registers, which spill at four waves per SIMD, and at three
 // were slower (530-580 us).
 //
-// What bounds it: VALU issue, busy 81 % of the time at 256^3; HBM moves
-// 4.5 TB/s.  Per step, pair against k_step: 418 / 645 us at 256^3, 55 / 83 us
+// What bounds it: VALU issue, busy 79-81 % of the time at 256^3; HBM moves
+// 4.5-5.1 TB/s (over cards: the halo lines that are read again vary).  Per step, pair against k_step: 418 / 645 us at 256^3, 55 / 83 us
 // at 128^3, 60 / 104 us at 181x118x77 (rows off the cache lines), 28 / 38 us
 // at 96^3; with force and scalar 76 / 108 us at 128^3.  binary16 levels stay
 // with k_step: it already issues VALU instructions 87 % of the time.
@@ -609,7 +609,7 @@ int launch_step_pair(const cslbm_level* L, const void* fin, void* fout, const fl
         return check_launch("k_step_pair_box");
     }
     const bool narrow = narrow_tiles(L);
-    // at most twelve waves, three per SIMD (the scalar takes 154-167 VGPRs)
+    // at most twelve waves (32 x 16: ten), three per SIMD (the scalar takes 154-167 VGPRs)
     if (gin && L->force) {
         if (narrow)
             launch_pair<true, true, 32, 16, 3>(a, stream);

@@ -6,7 +6,9 @@ smoke scalar ``s = sum_i g_i``.  Gradients with respect to theta and the
 initial populations come from the hand-written adjoint step of libcslbm
 (``cslbm_adjoint_step``); only every ``every``-th state is kept during the
 forward pass and each segment is recomputed with ``cslbm_step_store`` in the
-backward pass.  Tensors are dense: theta [3][N], h0 [27][N] shifted
+backward pass, bit for bit the states that the forward pass went through
+(``cslbm_step`` may compute two steps per launch; its states are those of
+single steps).  Tensors are dense: theta [3][N], h0 [27][N] shifted
 populations f - w, g0 [7][N].
 
 ``MultiscaleRollout`` does the same for the reference steps of a hierarchy
